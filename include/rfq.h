@@ -179,7 +179,7 @@ rfq_status rfq_gemm_split_noalloc(const uint8_t *q_codes, const uint8_t *q_scale
  * Workspace rfq_gemm_split uses for this shape: parts * M * N * 4 bytes for
  * the fp32 partials (at most 32 MiB), or 0 where it does not split (up to
  * 32 rows, 23 with K >= 12288, except the uneven few-row grids above;
- * 33-64 rows with 11264 <= N < 16384, K not a multiple of 512,
+ * 33-64 rows with 11264 <= N < 16384, a single group of 512 columns,
  * more than 128 tiles of 128 x 128 with K < 8192 or more than 192, or sizes
  * that rfq_gemm rejects).  Assumes 16-byte aligned scale tensors (with others the
  * product runs unsplit).  Host-only; no device call.

@@ -1,6 +1,8 @@
 // RFQ product on the gfx950 block-scaled FP4 matrix cores (Eq. 11,
 // Algorithm 1 with the fallback indicator phi = 1, or phi = 0 without the
-// residual operand):
+// residual operand): the choice of the kernel, and the general kernel, which
+// serves what the few-row and large-tile kernels do not take (scale tensors
+// that are not 16-byte aligned, code tensors past their 2 or 4 GiB):
 //
 //   Z[m][n] = sum_k q[m][k] w[n][k] * Sq[m][k/32] Sw[n][k/32]
 //           + sum_k r[m][k] w[n][k] * Sr[m][k/32] Sw[n][k/32]
@@ -313,10 +315,16 @@ hipError_t launch_tile(const uint8_t *qc, const uint8_t *qs, const uint8_t *rc,
 
 }  // namespace
 
+// The few-row and large-tile kernels take any K: where it is not a multiple
+// of 512 they run with a short last group or stage.  Against the general
+// kernel (bf16 Z): 6 rows x 4096 x 11008 69.6 -> 9.2 us, 64 x 4096 x 2880
+// 35.0 -> 8.9, 1000 x 5000 x 2912 76.4 -> 30.4, 4096 x 4096 x 11008 335.5 ->
+// 173.3; at a block or two (8 x 8 x 32, 64 x 256 x 256) both take a launch.
+//
 // The few-row kernel takes the product (shape conditions only; alignment and
 // size conditions of the kernels are checked where they are dispatched).
-static bool few_rows_chosen(int64_t M, int64_t N, int64_t K) {
-  return M <= kSkinnyMaxRows && (K % 512) == 0 && !large_tiles_beat_few_rows(M, N);
+static bool few_rows_chosen(int64_t M, int64_t N) {
+  return M <= kSkinnyMaxRows && !large_tiles_beat_few_rows(M, N);
 }
 
 // With a workspace the split product replaces the few-row kernel where it
@@ -338,8 +346,8 @@ static bool few_rows_beat_split(int64_t M, int64_t N, int64_t K) {
 }
 
 int64_t gemm_split_bytes(int64_t M, int64_t N, int64_t K) {
-  if (M <= 0 || N <= 0 || (K % 512) != 0) return 0;
-  if (few_rows_chosen(M, N, K) && few_rows_beat_split(M, N, K)) {
+  if (M <= 0 || N <= 0 || K < 32 || (K % 32) != 0) return 0;
+  if (few_rows_chosen(M, N) && few_rows_beat_split(M, N, K)) {
     const int parts = skinny_split_parts(M, N, K);
     return parts > 1 ? int64_t(parts) * M * N * 4 : 0;
   }
@@ -358,7 +366,7 @@ hipError_t launch_gemm(const uint8_t *q_codes, const uint8_t *q_scales,
     plan = splitk_plan(M, N, K);
     if (plan.work_bytes > work_bytes) plan = SplitPlan{1, K, 0};
   }
-  const bool split = plan.parts > 1 && !(few_rows_chosen(M, N, K) && few_rows_beat_split(M, N, K));
+  const bool split = plan.parts > 1 && !(few_rows_chosen(M, N) && few_rows_beat_split(M, N, K));
   if (gemm_skinny_applies(q_scales, r_scales, w_scales, M, N, K) && !split &&
       !(large && large_tiles_beat_few_rows(M, N))) {
     const int parts = work ? skinny_split_parts(M, N, K) : 1;

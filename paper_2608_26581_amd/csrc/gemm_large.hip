@@ -1,5 +1,5 @@
-// RFQ product, large-tile kernel for K a multiple of 512 (Eq. 11, Algorithm 1
-// with phi = 1; phi = 0 without the residual operand).
+// RFQ product, large-tile kernel (Eq. 11, Algorithm 1 with phi = 1; phi = 0
+// without the residual operand).
 //
 // Output tile 256 x 256 per workgroup of 8 waves (4 x 2, each wave 64 x 128
 // = 2 x 4 fragments of 32 x 32), one workgroup per CU and two waves per SIMD:
@@ -272,7 +272,15 @@ constexpr int kPhiMapMaxBytes = Big::kWaveRows * ((1 << 20) / kPhiK);
 // copies of the tile grid, copy s multiplying K columns [s ksplit, (s + 1)
 // ksplit) (ksplit a multiple of 512) and writing its fp32 partial product to
 // z + s M N.
-template <class C, bool RES, bool ZBF16, bool SWIGLU, bool HRES, bool PHI, bool SPLIT = false>
+//
+// GK: any K a multiple of 32 (without it a multiple of 512).  The last stage
+// may then hold 1 to 4 blocks: the chunks of blocks past K get offsets past
+// the buffer's end and load as zeros, and their scale bytes are masked to 0
+// (a neighbouring row's byte could be NaN).  A row's scale bytes start at any
+// byte: they are loaded as the five aligned dwords that hold 16 of them and
+// shifted into place when a stage's word is written to LDS.
+template <class C, bool RES, bool ZBF16, bool SWIGLU, bool HRES, bool PHI, bool SPLIT = false,
+          bool GK = false>
 __device__ __forceinline__ void gemm_tile(
     const uint8_t *__restrict__ qc, const uint8_t *__restrict__ qs,
     const uint8_t *__restrict__ rc, const uint8_t *__restrict__ rs,
@@ -305,7 +313,9 @@ __device__ __forceinline__ void gemm_tile(
   const int lane = tid & 63, wave = tid >> 6;
   const int wm = wave / C::kWaveCols, wn = wave % C::kWaveCols;
   const int64_t kbytes = K / 2, kblocks = K / 32;
-  const int nstages = (int)((SPLIT ? min(ksplit, K - kb) : K) / kStageK);
+  // MX blocks of this workgroup's K range, and the stages that hold them.
+  const int nblocks = (int)((SPLIT ? min(ksplit, K - kb) : K) / 32);
+  const int nstages = GK ? (nblocks + 3) / 4 : nblocks / 4;
 
   const int trow = tid / 4, tcol = 16 * (tid & 3);
   auto rsrc = [](const uint8_t *p, int64_t bytes) {
@@ -314,8 +324,12 @@ __device__ __forceinline__ void gemm_tile(
   };
   const __amdgpu_buffer_rsrc_t cq = rsrc(qc, M * kbytes), cr = rsrc(RES ? rc : qc, M * kbytes),
                                cw = rsrc(wc, N * kbytes);
-  const __amdgpu_buffer_rsrc_t sq = rsrc(qs, M * kblocks), sr = rsrc(RES ? rs : qs, M * kblocks),
-                               sw = rsrc(ws, N * kblocks);
+  // Scale ranges end at a whole dword (the tensors start 16-byte aligned, so
+  // a dword that holds a valid byte lies in the same 16 bytes of memory).
+  auto whole = [](int64_t bytes) { return GK ? (bytes + 3) / 4 * 4 : bytes; };
+  const __amdgpu_buffer_rsrc_t sq = rsrc(qs, whole(M * kblocks)),
+                               sr = rsrc(RES ? rs : qs, whole(M * kblocks)),
+                               sw = rsrc(ws, whole(N * kblocks));
   // Chunk u of this thread: buffer row trow + kRPL u, chunk tid mod 4.
   // Operand of buffer row block u (kRPL rows): 0 q, 1 r, 2 w.
   auto op_of = [](int u) { return u * kRPL < kBM ? 0 : (RES && u * kRPL < 2 * kBM ? 1 : 2); };
@@ -332,7 +346,7 @@ __device__ __forceinline__ void gemm_tile(
   auto sbr = [&](int v) { return min(tid + kThreads * v, L::kRows - 1); };
   auto sop = [&](int br) { return br < kBM ? 0 : (RES && br < 2 * kBM ? 1 : 2); };
   int s_op[L::kScaleLoads];
-  uint32_t s_off[L::kScaleLoads];
+  uint32_t s_off[L::kScaleLoads], s_sh[GK ? L::kScaleLoads : 1];
 #pragma unroll
   for (int v = 0; v < L::kScaleLoads; ++v) {
     const int br = sbr(v);
@@ -340,12 +354,17 @@ __device__ __forceinline__ void gemm_tile(
     const int o = sop(br);
     s_off[v] = o == 2 ? (uint32_t)min(n0 + br - L::kWRow, N - 1) * (uint32_t)kblocks
                       : (uint32_t)min(m0 + br - (o == 1 ? kBM : 0), M - 1) * (uint32_t)kblocks;
+    if constexpr (GK) {
+      s_sh[v] = s_off[v] & 3u;
+      s_off[v] &= ~3u;
+    }
   }
 
   // pf: the stage in flight (registers); grp: 16 scale bytes (kGroup
   // stages) of this thread's scale rows.
   u32x4 pf[L::kLoads];
   u32x4 grp[L::kScaleLoads];
+  uint32_t grp4[GK ? L::kScaleLoads : 1];   // GK: the fifth dword
   // Offset of a skipped load: at or past the end of any operand below
   // 2 GiB of codes (for larger operands it may land inside the buffer,
   // which only costs the fetch: the data is never read).
@@ -356,10 +375,13 @@ __device__ __forceinline__ void gemm_tile(
   // zeros without a memory access (the block's LDS rows are then never
   // read).
   auto load_stage = [&](int st, int rmask) {
+    // GK (operands below 2 GiB): past K, an offset past every buffer's end.
+    const uint32_t past = GK && 4 * st + (tid & 3) >= nblocks ? kSkipOffset : 0;
 #pragma unroll
     for (int u = 0; u < L::kLoads; ++u) {
       const int o = op_of(u);
       uint32_t off = o == 2 ? w_off[u - L::kWRow / kRPL] : a_off[u % (kBM / kRPL)];
+      if constexpr (GK) off |= past;
       if constexpr (PHI && RES)
         if (o == 1) off = ((rmask >> (u - kBM / kRPL)) & 1) ? off : kSkipOffset;
       pf[u] = __builtin_amdgcn_raw_buffer_load_b128(o == 0 ? cq : (o == 1 ? cr : cw), off,
@@ -368,20 +390,31 @@ __device__ __forceinline__ void gemm_tile(
   };
   auto load_group = [&](int gi) {
 #pragma unroll
-    for (int v = 0; v < L::kScaleLoads; ++v)
-      grp[v] = __builtin_amdgcn_raw_buffer_load_b128(s_op[v] == 0 ? sq : (s_op[v] == 1 ? sr : sw),
-                                                     s_off[v], kb_scale + 16 * gi, 0);
+    for (int v = 0; v < L::kScaleLoads; ++v) {
+      const __amdgpu_buffer_rsrc_t s = s_op[v] == 0 ? sq : (s_op[v] == 1 ? sr : sw);
+      grp[v] = __builtin_amdgcn_raw_buffer_load_b128(s, s_off[v], kb_scale + 16 * gi, 0);
+      if constexpr (GK)
+        grp4[v] = __builtin_amdgcn_raw_buffer_load_b32(s, s_off[v] + 16, kb_scale + 16 * gi, 0);
+    }
   };
-  // Writes the register stage and word `word` of the scale group to LDS.
-  auto store_stage = [&](int buf, auto word_tag) {
+  // Writes the register stage (stage st) and word `word` of the scale group
+  // to LDS.
+  auto store_stage = [&](int buf, int st, auto word_tag) {
     constexpr int W = decltype(word_tag)::value;
+    const int live = nblocks - 4 * st;               // GK: blocks of the stage within K
+    const uint32_t smask = live >= 4 ? 0xFFFFFFFFu : (1u << (8 * live)) - 1u;
     uint8_t *b = smem + buf * L::kStageBytes;
 #pragma unroll
     for (int u = 0; u < L::kLoads; ++u)
       *reinterpret_cast<u32x4 *>(b + chunk_off(trow + kRPL * u, tid & 3)) = pf[u];
 #pragma unroll
-    for (int v = 0; v < L::kScaleLoads; ++v)
-      *reinterpret_cast<uint32_t *>(b + L::kDataBytes + 4 * sbr(v)) = grp[v][W];
+    for (int v = 0; v < L::kScaleLoads; ++v) {
+      uint32_t word = grp[v][W];
+      if constexpr (GK)
+        word = __builtin_amdgcn_alignbyte(W == 3 ? grp4[v] : grp[v][W < 3 ? W + 1 : 3], word,
+                                          s_sh[v]) & smask;
+      *reinterpret_cast<uint32_t *>(b + L::kDataBytes + 4 * sbr(v)) = word;
+    }
   };
 
   const int frow = lane & 31, h = lane >> 5;
@@ -487,7 +520,7 @@ __device__ __forceinline__ void gemm_tile(
   if constexpr (PHI) __syncthreads();   // the indicator words
   load_group(0);
   load_stage(0, PHI ? res_mask(0) : 3);
-  store_stage(0, W0{});
+  store_stage(0, 0, W0{});
   __builtin_amdgcn_sched_barrier(0);
   load_stage(min(1, nstages - 1), PHI ? res_mask(min(1, nstages - 1)) : 3);
   asm volatile("" ::: "memory");
@@ -514,7 +547,7 @@ __device__ __forceinline__ void gemm_tile(
     constexpr bool RELOAD = decltype(reload_tag)::value;
     const int buf = st & 1, nbuf = buf ^ 1;
     constexpr int kW = HANDOVER ? L::kLoads + L::kScaleLoads : 0;
-    constexpr int kV = (HANDOVER ? L::kLoads : 0) + (RELOAD ? L::kScaleLoads : 0);
+    constexpr int kV = (HANDOVER ? L::kLoads : 0) + (RELOAD ? (GK ? 2 : 1) * L::kScaleLoads : 0);
     int on = 1, lmask = 3;
     if constexpr (PHI) {
       on = (phi_word(st) >> (8 * wm_u)) & 0xFFu;
@@ -527,7 +560,7 @@ __device__ __forceinline__ void gemm_tile(
     read_scales(buf, sc);
     read_a(buf, 0, 0, a0);
     read_a(buf, 0, 1, a1);
-    if constexpr (HANDOVER) store_stage(nbuf, word_tag);
+    if constexpr (HANDOVER) store_stage(nbuf, st + 1, word_tag);
     if constexpr (PHI) {
       mma_part(w, a0, sc, 0, S0{}, Prim{});
       mma_part(w, a1, sc, 1, S0{}, Prim{});
@@ -573,8 +606,8 @@ __device__ __forceinline__ void gemm_tile(
     __syncthreads();
   };
 
-  // nstages is a multiple of kGroup; stage st writes scale word
-  // (st+1) mod kGroup, so unrolling by kGroup keeps it static.  The scale
+  // Stage st writes scale word (st+1) mod kGroup, so unrolling by kGroup
+  // keeps it static (the rest are the last 1 to kGroup stages).  The scale
   // group is refetched after its last word is written.  (The last group's
   // stages are written as conditional: unconditional straight-line copies
   // make the register allocator spill.)
@@ -659,23 +692,23 @@ __device__ __forceinline__ void gemm_tile(
       int64_t K, void *__restrict__ z, SwigluOut so, const uint8_t *__restrict__ phi,      \
       int64_t ksplit
 
-template <bool RES, bool ZBF16, bool SWIGLU = false, bool HRES = false, bool PHI = false>
+template <bool RES, bool ZBF16, bool SWIGLU, bool HRES, bool PHI, bool GK>
 __global__ __launch_bounds__(Big::kThreads, 2) void rfq_gemm_large_kernel(RFQ_TILE_ARGS) {
-  gemm_tile<Big, RES, ZBF16, SWIGLU, HRES, PHI>(qc, qs, rc, rs, wc, ws, M, N, K, z, so, phi,
-                                                ksplit);
+  gemm_tile<Big, RES, ZBF16, SWIGLU, HRES, PHI, false, GK>(qc, qs, rc, rs, wc, ws, M, N, K, z, so,
+                                                           phi, ksplit);
 }
 
-template <bool RES, bool ZBF16, bool SWIGLU = false, bool HRES = false>
+template <bool RES, bool ZBF16, bool SWIGLU, bool HRES, bool GK>
 __global__ __launch_bounds__(Mid::kThreads, 3) void rfq_gemm_mid_kernel(RFQ_TILE_ARGS) {
-  gemm_tile<Mid, RES, ZBF16, SWIGLU, HRES, false>(qc, qs, rc, rs, wc, ws, M, N, K, z, so, phi,
-                                                  ksplit);
+  gemm_tile<Mid, RES, ZBF16, SWIGLU, HRES, false, false, GK>(qc, qs, rc, rs, wc, ws, M, N, K, z,
+                                                             so, phi, ksplit);
 }
 
 // K split over several workgroups per 128 x 128 tile: fp32 partial products.
-template <bool RES>
+template <bool RES, bool GK>
 __global__ __launch_bounds__(Mid::kThreads, 3) void rfq_gemm_split_kernel(RFQ_TILE_ARGS) {
-  gemm_tile<Mid, RES, false, false, false, false, true>(qc, qs, rc, rs, wc, ws, M, N, K, z, so,
-                                                        phi, ksplit);
+  gemm_tile<Mid, RES, false, false, false, false, true, GK>(qc, qs, rc, rs, wc, ws, M, N, K, z,
+                                                            so, phi, ksplit);
 }
 #undef RFQ_TILE_ARGS
 
@@ -712,20 +745,25 @@ __global__ __launch_bounds__(256) void splitk_sum_kernel(const float *__restrict
   }
 }
 
-template <class C, bool RES, bool ZBF16, bool SWIGLU = false, bool HRES = false, bool PHI = false>
+template <class C, bool RES, bool ZBF16, bool SWIGLU = false, bool HRES = false, bool PHI = false,
+          bool GK = false>
 hipError_t launch(const uint8_t *qc, const uint8_t *qs, const uint8_t *rc,
                   const uint8_t *rs, const uint8_t *wc, const uint8_t *ws,
                   int64_t M, int64_t N, int64_t K, void *z, hipStream_t stream,
                   const SwigluOut &so = SwigluOut{}, const uint8_t *phi = nullptr) {
+  if constexpr (!SWIGLU && !GK)
+    if (K % (kStageK * kGroup))
+      return launch<C, RES, ZBF16, SWIGLU, HRES, PHI, true>(qc, qs, rc, rs, wc, ws, M, N, K, z,
+                                                            stream, so, phi);
   using L = Layout<C, RES>;
   static_assert((C::kThreads / 64) * Epi<ZBF16>::kWaveBytes <= L::kBytes, "epilogue staging fits");
   void (*kern)(const uint8_t *, const uint8_t *, const uint8_t *, const uint8_t *,
                const uint8_t *, const uint8_t *, int64_t, int64_t, int64_t, void *, SwigluOut,
                const uint8_t *, int64_t);
   if constexpr (std::is_same<C, Big>::value)
-    kern = rfq_gemm_large_kernel<RES, ZBF16, SWIGLU, HRES, PHI>;
+    kern = rfq_gemm_large_kernel<RES, ZBF16, SWIGLU, HRES, PHI, GK>;
   else
-    kern = rfq_gemm_mid_kernel<RES, ZBF16, SWIGLU, HRES>;
+    kern = rfq_gemm_mid_kernel<RES, ZBF16, SWIGLU, HRES, GK>;
   // LDS: the two stage buffers, then (PHI) the rows of the indicator map.
   constexpr int kMaxBytes = L::kBytes + (PHI ? kPhiMapMaxBytes : 0);
   const int phi_bytes =
@@ -741,13 +779,17 @@ hipError_t launch(const uint8_t *qc, const uint8_t *qs, const uint8_t *rc,
 
 // K split into `parts` ranges of ksplit columns (a multiple of 512): the
 // partial products go to work[parts][M][N] (fp32), then one pass adds them.
-template <bool RES>
+template <bool RES, bool GK = false>
 hipError_t launch_split(const uint8_t *qc, const uint8_t *qs, const uint8_t *rc,
                         const uint8_t *rs, const uint8_t *wc, const uint8_t *ws, int64_t M,
                         int64_t N, int64_t K, void *z, bool z_bf16, float *work, int parts,
                         int64_t ksplit, hipStream_t stream) {
+  if constexpr (!GK)
+    if (K % (kStageK * kGroup))
+      return launch_split<RES, true>(qc, qs, rc, rs, wc, ws, M, N, K, z, z_bf16, work, parts,
+                                     ksplit, stream);
   using L = Layout<Mid, RES>;
-  auto kern = rfq_gemm_split_kernel<RES>;
+  auto kern = rfq_gemm_split_kernel<RES, GK>;
   static std::atomic<bool> attr_done[kMaxDevices];
   hipError_t e = set_lds_limit(attr_done, reinterpret_cast<const void *>(kern), L::kBytes);
   if (e != hipSuccess) return e;
@@ -805,7 +847,7 @@ hipError_t launch_splitk_sum(const float *work, int parts, int64_t mn, void *z, 
 
 SplitPlan splitk_plan(int64_t M, int64_t N, int64_t K, int parts_wanted) {
   SplitPlan p{1, K, 0};
-  const int64_t units = K / (kStageK * kGroup);
+  const int64_t units = (K + kStageK * kGroup - 1) / (kStageK * kGroup);
   if (!use_mid_tiles(M, N) || units < 2) return p;
   int want = parts_wanted;
   if (want <= 0) want = splitk_default_parts(M, N, K);
@@ -842,10 +884,10 @@ bool gemm_large_applies(const uint8_t *q_scales, const uint8_t *r_scales,
   const uintptr_t a = reinterpret_cast<uintptr_t>(q_scales) |
                       reinterpret_cast<uintptr_t>(r_scales) |
                       reinterpret_cast<uintptr_t>(w_scales);
-  // Byte offsets inside an operand are 32-bit.
-  const int64_t limit = int64_t(1) << 32;
-  return (K % (kStageK * kGroup)) == 0 && (a & 15) == 0 && M * (K / 2) < limit &&
-         N * (K / 2) < limit;
+  // Byte offsets inside an operand are 32-bit; where K does not divide by 512
+  // their top bit marks the loads past K.
+  const int64_t limit = int64_t(1) << ((K % (kStageK * kGroup)) == 0 ? 32 : 31);
+  return (a & 15) == 0 && M * (K / 2) < limit && N * (K / 2) < limit;
 }
 
 // 256-row tile rows that run 256 x 256 tiles where those do not fill their

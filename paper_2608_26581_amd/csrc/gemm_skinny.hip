@@ -58,8 +58,9 @@ constexpr int kSkThreads = 256;     // 4 waves, one K range each
 constexpr int kSkRows = 16;         // W rows and activation rows per workgroup
 constexpr int kSkGroupK = 512;      // K values per load group (4 k-steps)
 
-struct XGroup { u32x4 q[4], r[4], qs, rs; };
-struct WGroup { u32x4 c[4], s; };
+// (qs4, rs4, s4: the fifth dword of unaligned scale bytes.)
+struct XGroup { u32x4 q[4], r[4], qs, rs; uint32_t qs4, rs4; };
+struct WGroup { u32x4 c[4], s; uint32_t s4; };
 
 // 16 code bytes as the MFMA's 8-register FP4 operand (upper half unused).
 __device__ __forceinline__ v8i frag(const u32x4 &d) {
@@ -186,7 +187,13 @@ __device__ __forceinline__ void reduce_store(v4f (&partial)[kSkThreads / 64][64]
 template <int F>
 struct WPair { WGroup f[F]; };
 
-template <bool RES, bool ZBF16, int S, int F>
+// GK: any K a multiple of 32 (without it a multiple of 512).  The last group
+// may then hold fewer than 16 blocks: W's codes past K load as zeros (so the
+// activation codes there, a neighbouring row's, do not matter) and the scale
+// bytes past K are masked to 0 (a neighbouring row's could be NaN).  A row's
+// scale bytes start at any byte: the five aligned dwords that hold a group's
+// 16 are loaded and shifted into place.
+template <bool RES, bool ZBF16, int S, int F, bool GK>
 __global__ __launch_bounds__(kSkThreads, F == 1 ? 3 : (F == 2 ? 2 : 1)) void rfq_gemm_skinny_kernel(
     const uint8_t *__restrict__ qc, const uint8_t *__restrict__ qs,
     const uint8_t *__restrict__ rc, const uint8_t *__restrict__ rs,
@@ -204,12 +211,35 @@ __global__ __launch_bounds__(kSkThreads, F == 1 ? 3 : (F == 2 ? 2 : 1)) void rfq
 
   // This wave's groups of 4 k-steps: [gb, ge) of K / 512, within this
   // workgroup's part [pb, pe).
-  const int ngroups = (int)(K / kSkGroupK);
+  const int ngroups = (int)((K + kSkGroupK - 1) / kSkGroupK);
   const int part = (int)blockIdx.z, parts = (int)gridDim.z;
   const int pb = (ngroups * part) / parts, pe = (ngroups * (part + 1)) / parts;
   const int gb = pb + ((pe - pb) * wave) / 4, ge = pb + ((pe - pb) * (wave + 1)) / 4;
 
-  const __amdgpu_buffer_rsrc_t rwc = rsrc(wc, N * kbytes), rws = rsrc(ws, N * kblocks);
+  // Scale ranges end at a whole dword (the tensors start 16-byte aligned, so
+  // a dword that holds a valid byte lies in the same 16 bytes of memory).
+  auto whole = [](int64_t bytes) { return GK ? (bytes + 3) / 4 * 4 : bytes; };
+  const __amdgpu_buffer_rsrc_t rwc = rsrc(wc, N * kbytes), rws = rsrc(ws, whole(N * kblocks));
+  // The 16 scale bytes of group gi of the row whose bytes start at `off`
+  // (an offset past the buffer's end: zeros): raw dwords, then (GK) shifted.
+  auto load_scales = [&](const __amdgpu_buffer_rsrc_t &r, uint32_t off, int gi, u32x4 &s,
+                         uint32_t &s4) {
+    s = __builtin_amdgcn_raw_buffer_load_b128(r, GK ? off & ~3u : off, gi * (kSkGroupK / 32), 0);
+    if constexpr (GK)
+      s4 = __builtin_amdgcn_raw_buffer_load_b32(r, (off & ~3u) + 16, gi * (kSkGroupK / 32), 0);
+  };
+  auto place_scales = [&](const u32x4 &s, uint32_t s4, uint32_t off, int gi) {
+    if constexpr (!GK) return s;
+    const uint32_t d[5] = {s.x, s.y, s.z, s.w, s4};
+    u32x4 o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int live = (int)kblocks - 16 * gi - 4 * j;     // bytes of this word within K
+      const uint32_t m = live >= 4 ? 0xFFFFFFFFu : (live <= 0 ? 0u : (1u << (8 * live)) - 1u);
+      o[j] = __builtin_amdgcn_alignbyte(d[j + 1], d[j], off & 3u) & m;
+    }
+    return o;
+  };
   uint32_t w_off[F], ws_off[F];
 #pragma unroll
   for (int f = 0; f < F; ++f) {
@@ -221,18 +251,22 @@ __global__ __launch_bounds__(kSkThreads, F == 1 ? 3 : (F == 2 ? 2 : 1)) void rfq
 #pragma unroll
     for (int f = 0; f < F; ++f) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        w.f[f].c[j] = __builtin_amdgcn_raw_buffer_load_b128(rwc, w_off[f],
-                                                            gi * (kSkGroupK / 2) + 64 * j, 0);
-      w.f[f].s = __builtin_amdgcn_raw_buffer_load_b128(rws, ws_off[f], gi * (kSkGroupK / 32), 0);
+      for (int j = 0; j < 4; ++j) {
+        const bool past = GK && 16 * gi + 4 * j + g >= kblocks;
+        w.f[f].c[j] = __builtin_amdgcn_raw_buffer_load_b128(
+            rwc, past ? 0x80000000u : w_off[f], gi * (kSkGroupK / 2) + 64 * j, 0);
+      }
+      load_scales(rws, ws_off[f], gi, w.f[f].s, w.f[f].s4);
     }
   };
 
   const __amdgpu_buffer_rsrc_t rxa = rsrc(qc, M * kbytes), rxb = rsrc(RES ? rc : qc, M * kbytes);
-  const __amdgpu_buffer_rsrc_t rxs = rsrc(qs, M * kblocks), rxt = rsrc(RES ? rs : qs, M * kblocks);
+  const __amdgpu_buffer_rsrc_t rxs = rsrc(qs, whole(M * kblocks)),
+                               rxt = rsrc(RES ? rs : qs, whole(M * kblocks));
+  auto x_row = [&](int sl) { return (uint32_t)min(m0 + kSkRows * sl + row, M - 1); };
   // Activation codes of slice sl of group gi (rows past M clamped to the last).
   auto load_x = [&](XGroup &xg, int gi, int sl) {
-    const uint32_t xm = (uint32_t)min(m0 + kSkRows * sl + row, M - 1);
+    const uint32_t xm = x_row(sl);
     const bool live = sl < slices;
     const uint32_t xc_off = live ? xm * (uint32_t)kbytes + 16 * g : 0x80000000u;
     const uint32_t xs_off = live ? xm * (uint32_t)kblocks : 0x80000000u;
@@ -242,9 +276,8 @@ __global__ __launch_bounds__(kSkThreads, F == 1 ? 3 : (F == 2 ? 2 : 1)) void rfq
       if constexpr (RES)
         xg.r[j] = __builtin_amdgcn_raw_buffer_load_b128(rxb, xc_off, gi * (kSkGroupK / 2) + 64 * j, 0);
     }
-    xg.qs = __builtin_amdgcn_raw_buffer_load_b128(rxs, xs_off, gi * (kSkGroupK / 32), 0);
-    if constexpr (RES)
-      xg.rs = __builtin_amdgcn_raw_buffer_load_b128(rxt, xs_off, gi * (kSkGroupK / 32), 0);
+    load_scales(rxs, xs_off, gi, xg.qs, xg.qs4);
+    if constexpr (RES) load_scales(rxt, xs_off, gi, xg.rs, xg.rs4);
   };
 
   v4f acc[S][F];
@@ -253,14 +286,20 @@ __global__ __launch_bounds__(kSkThreads, F == 1 ? 3 : (F == 2 ? 2 : 1)) void rfq
 #pragma unroll
     for (int f = 0; f < F; ++f) acc[sl][f] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 
-  auto compute = [&](const WPair<F> &w, const XGroup &xg, v4f (&a)[F]) {
+  auto compute = [&](const WPair<F> &w, const XGroup &xg, int gi, int sl, v4f (&a)[F]) {
+    const uint32_t xs_off = x_row(sl) * (uint32_t)kblocks;
+    const u32x4 qsc = place_scales(xg.qs, xg.qs4, xs_off, gi);
+    const u32x4 rsc = RES ? place_scales(xg.rs, xg.rs4, xs_off, gi) : qsc;
+    u32x4 wsc[F];
+#pragma unroll
+    for (int f = 0; f < F; ++f) wsc[f] = place_scales(w.f[f].s, w.f[f].s4, ws_off[f], gi);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
 #pragma unroll
       for (int f = 0; f < F; ++f) {
-        const uint32_t wsc = scale_of(w.f[f].s, j, g);
-        a[f] = mma16(w.f[f].c[j], wsc, xg.q[j], scale_of(xg.qs, j, g), a[f]);
-        if constexpr (RES) a[f] = mma16(w.f[f].c[j], wsc, xg.r[j], scale_of(xg.rs, j, g), a[f]);
+        const uint32_t wb = scale_of(wsc[f], j, g);
+        a[f] = mma16(w.f[f].c[j], wb, xg.q[j], scale_of(qsc, j, g), a[f]);
+        if constexpr (RES) a[f] = mma16(w.f[f].c[j], wb, xg.r[j], scale_of(rsc, j, g), a[f]);
       }
     }
   };
@@ -277,7 +316,7 @@ __global__ __launch_bounds__(kSkThreads, F == 1 ? 3 : (F == 2 ? 2 : 1)) void rfq
       XGroup &nxt = (sl & 1) ? xa : xb;
       if (sl + 1 < S) load_x(nxt, gi, sl + 1);
       else if (gi + 1 < ge) load_x(nxt, gi + 1, 0);
-      if (sl < slices) compute(w, cur, acc[sl]);
+      if (sl < slices) compute(w, cur, gi, sl, acc[sl]);
     }
   };
   if (gb < ge) {
@@ -513,14 +552,18 @@ __global__ __launch_bounds__(kSkThreads, (XF32 || kStFrags > 1) ? 1 : 2) void rf
   }
 }
 
-template <bool RES, bool ZBF16, int S, int F = 2>
+template <bool RES, bool ZBF16, int S, int F>
 hipError_t launch_sk_s(const uint8_t *qc, const uint8_t *qs, const uint8_t *rc, const uint8_t *rs,
                        const uint8_t *wc, const uint8_t *ws, int64_t M, int64_t N, int64_t K,
                        void *z, int parts, hipStream_t stream) {
   const dim3 grid((unsigned)((N + F * kSkRows - 1) / (F * kSkRows)),
                   (unsigned)((M + S * kSkRows - 1) / (S * kSkRows)), (unsigned)parts);
-  rfq_gemm_skinny_kernel<RES, ZBF16, S, F><<<grid, dim3(kSkThreads), 0, stream>>>(
-      qc, qs, rc, rs, wc, ws, M, N, K, z);
+  if (K % kSkGroupK)
+    rfq_gemm_skinny_kernel<RES, ZBF16, S, F, true><<<grid, dim3(kSkThreads), 0, stream>>>(
+        qc, qs, rc, rs, wc, ws, M, N, K, z);
+  else
+    rfq_gemm_skinny_kernel<RES, ZBF16, S, F, false><<<grid, dim3(kSkThreads), 0, stream>>>(
+        qc, qs, rc, rs, wc, ws, M, N, K, z);
   return hipGetLastError();
 }
 
@@ -628,8 +671,7 @@ bool gemm_skinny_applies(const uint8_t *q_scales, const uint8_t *r_scales,
                       reinterpret_cast<uintptr_t>(r_scales) |
                       reinterpret_cast<uintptr_t>(w_scales);
   const int64_t limit = int64_t(1) << 31;
-  return M <= kSkinnyMaxRows && (K % kSkGroupK) == 0 && (a & 15) == 0 &&
-         M * (K / 2) < limit && N * (K / 2) < limit;
+  return M <= kSkinnyMaxRows && (a & 15) == 0 && M * (K / 2) < limit && N * (K / 2) < limit;
 }
 
 hipError_t launch_gemm_skinny(const uint8_t *q_codes, const uint8_t *q_scales,

@@ -63,8 +63,8 @@ hipError_t launch_gemm(const uint8_t *q_codes, const uint8_t *q_scales,
 // assuming 16-byte aligned scale tensors.
 int64_t gemm_split_bytes(int64_t M, int64_t N, int64_t K);
 
-// Large-tile product: K a multiple of 512, 16-byte aligned scale tensors and
-// code tensors below 4 GiB.
+// Large-tile product: 16-byte aligned scale tensors and code tensors below
+// 4 GiB (2 GiB where K is not a multiple of 512).
 bool gemm_large_applies(const uint8_t *q_scales, const uint8_t *r_scales,
                         const uint8_t *w_scales, int64_t M, int64_t N, int64_t K);
 hipError_t launch_gemm_large(const uint8_t *q_codes, const uint8_t *q_scales,
@@ -114,8 +114,7 @@ hipError_t launch_gemm_static_scratch(const uint8_t *q_codes, const uint8_t *q_s
 // occupies 32-40 CUs.
 bool large_tiles_beat_few_rows(int64_t M, int64_t N);
 
-// Product for few activation rows (M <= kSkinnyMaxRows, K a multiple of 512,
-// 16-byte aligned scale tensors, code tensors below 2 GiB): one workgroup per
+// Product for few activation rows (M <= kSkinnyMaxRows, 16-byte aligned scale tensors, code tensors below 2 GiB): one workgroup per
 // 16, 32 or 64 weight rows and up to 64 activation rows.
 constexpr int64_t kSkinnyMaxRows = 128;
 // Where it runs 64 weight rows per workgroup (5-64 activation rows at
