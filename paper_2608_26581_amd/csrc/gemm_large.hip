@@ -69,8 +69,10 @@ namespace {
 
 // Workgroup tile: WM x WN waves, each 64 rows x 32 FN columns (2 x FN
 // fragments of 32 x 32).
-template <int WM, int WN, int FN>
+// D: stages held in registers between their loads and their writes to LDS.
+template <int WM, int WN, int FN, int D>
 struct Tile {
+  static constexpr int kDepth = D;
   static constexpr int kThreads = 64 * WM * WN;
   static constexpr int kFM = 2, kFN = FN;
   static constexpr int kTM = 32 * kFM, kTN = 32 * FN;   // wave sub-tile
@@ -80,10 +82,14 @@ struct Tile {
   static constexpr int kRPL = kThreads / 4;             // buffer rows per load step (4 chunks a row)
 };
 // 256 x 256, 8 waves of 64 x 128, one workgroup per CU, two waves per SIMD.
-using Big = Tile<4, 2, 4>;
+using Big = Tile<4, 2, 4, 1>;
 // 128 x 128, 4 waves of 64 x 64, for products whose 256 x 256 tiles would
 // leave CUs idle; up to three workgroups per CU.
-using Mid = Tile<2, 2, 2>;
+using Mid = Tile<2, 2, 2, 1>;
+// The same with two stages in registers (loads two to three stages ahead of
+// their use), at most two workgroups per CU: for grids of at most one
+// workgroup per CU, where nothing else covers the loads' latency.
+using MidDeep = Tile<2, 2, 2, 2>;
 
 constexpr int kStageK = 128;
 constexpr int kRowBytes = kStageK / 2;
@@ -362,9 +368,13 @@ __device__ __forceinline__ void gemm_tile(
 
   // pf: the stage in flight (registers); grp: 16 scale bytes (kGroup
   // stages) of this thread's scale rows.
-  u32x4 pf[L::kLoads];
-  u32x4 grp[L::kScaleLoads];
-  uint32_t grp4[GK ? L::kScaleLoads : 1];   // GK: the fifth dword
+  constexpr int D = C::kDepth;
+  u32x4 pf[D][L::kLoads];
+  struct Group {
+    u32x4 w[L::kScaleLoads];
+    uint32_t w4[GK ? L::kScaleLoads : 1];   // GK: the fifth dword
+  };
+  Group grp, grpn;   // D > 1: the next group too
   // Offset of a skipped load: at or past the end of any operand below
   // 2 GiB of codes (for larger operands it may land inside the buffer,
   // which only costs the fetch: the data is never read).
@@ -374,7 +384,8 @@ __device__ __forceinline__ void gemm_tile(
   // past the end of the buffer, which the buffer range check turns into
   // zeros without a memory access (the block's LDS rows are then never
   // read).
-  auto load_stage = [&](int st, int rmask) {
+  auto load_stage = [&](int st, int rmask, auto slot_tag) {
+    constexpr int SLOT = decltype(slot_tag)::value % D;
     // GK (operands below 2 GiB): past K, an offset past every buffer's end.
     const uint32_t past = GK && 4 * st + (tid & 3) >= nblocks ? kSkipOffset : 0;
 #pragma unroll
@@ -384,17 +395,17 @@ __device__ __forceinline__ void gemm_tile(
       if constexpr (GK) off |= past;
       if constexpr (PHI && RES)
         if (o == 1) off = ((rmask >> (u - kBM / kRPL)) & 1) ? off : kSkipOffset;
-      pf[u] = __builtin_amdgcn_raw_buffer_load_b128(o == 0 ? cq : (o == 1 ? cr : cw), off,
+      pf[SLOT][u] = __builtin_amdgcn_raw_buffer_load_b128(o == 0 ? cq : (o == 1 ? cr : cw), off,
                                                     kb_code + st * kRowBytes, 0);
     }
   };
-  auto load_group = [&](int gi) {
+  auto load_group = [&](Group &g, int gi) {
 #pragma unroll
     for (int v = 0; v < L::kScaleLoads; ++v) {
       const __amdgpu_buffer_rsrc_t s = s_op[v] == 0 ? sq : (s_op[v] == 1 ? sr : sw);
-      grp[v] = __builtin_amdgcn_raw_buffer_load_b128(s, s_off[v], kb_scale + 16 * gi, 0);
+      g.w[v] = __builtin_amdgcn_raw_buffer_load_b128(s, s_off[v], kb_scale + 16 * gi, 0);
       if constexpr (GK)
-        grp4[v] = __builtin_amdgcn_raw_buffer_load_b32(s, s_off[v] + 16, kb_scale + 16 * gi, 0);
+        g.w4[v] = __builtin_amdgcn_raw_buffer_load_b32(s, s_off[v] + 16, kb_scale + 16 * gi, 0);
     }
   };
   // Writes the register stage (stage st) and word `word` of the scale group
@@ -406,12 +417,12 @@ __device__ __forceinline__ void gemm_tile(
     uint8_t *b = smem + buf * L::kStageBytes;
 #pragma unroll
     for (int u = 0; u < L::kLoads; ++u)
-      *reinterpret_cast<u32x4 *>(b + chunk_off(trow + kRPL * u, tid & 3)) = pf[u];
+      *reinterpret_cast<u32x4 *>(b + chunk_off(trow + kRPL * u, tid & 3)) = pf[W % D][u];
 #pragma unroll
     for (int v = 0; v < L::kScaleLoads; ++v) {
-      uint32_t word = grp[v][W];
+      uint32_t word = grp.w[v][W];
       if constexpr (GK)
-        word = __builtin_amdgcn_alignbyte(W == 3 ? grp4[v] : grp[v][W < 3 ? W + 1 : 3], word,
+        word = __builtin_amdgcn_alignbyte(W == 3 ? grp.w4[v] : grp.w[v][W < 3 ? W + 1 : 3], word,
                                           s_sh[v]) & smask;
       *reinterpret_cast<uint32_t *>(b + L::kDataBytes + 4 * sbr(v)) = word;
     }
@@ -518,11 +529,23 @@ __device__ __forceinline__ void gemm_tile(
   };
   // ---- prologue: stage 0 into buffer 0, stage 1 in registers.
   if constexpr (PHI) __syncthreads();   // the indicator words
-  load_group(0);
-  load_stage(0, PHI ? res_mask(0) : 3);
+  const int last = nstages - 1;
+  auto prefetch = [&](int st, auto slot_tag) {
+    load_stage(min(st, last), PHI ? res_mask(min(st, last)) : 3, slot_tag);
+  };
+  load_group(grp, 0);
+  prefetch(0, W0{});
+  if constexpr (D > 1) {
+    prefetch(1, W1{});
+    load_group(grpn, min(1, last / kGroup));
+    if constexpr (D > 2) {
+      prefetch(2, W2{});
+      prefetch(3, W3{});
+    }
+  }
   store_stage(0, 0, W0{});
   __builtin_amdgcn_sched_barrier(0);
-  load_stage(min(1, nstages - 1), PHI ? res_mask(min(1, nstages - 1)) : 3);
+  prefetch(D, W0{});
   asm volatile("" ::: "memory");
   __syncthreads();
 
@@ -551,7 +574,7 @@ __device__ __forceinline__ void gemm_tile(
     int on = 1, lmask = 3;
     if constexpr (PHI) {
       on = (phi_word(st) >> (8 * wm_u)) & 0xFFu;
-      if constexpr (HANDOVER) lmask = res_mask(min(st + 2, nstages - 1));
+      if constexpr (HANDOVER) lmask = res_mask(min(st + 1 + D, last));
     }
     WFrag w;
     AFrag a0, a1;
@@ -579,8 +602,15 @@ __device__ __forceinline__ void gemm_tile(
     }
     region_end();
 
-    if constexpr (RELOAD) load_group((st + 2) / kGroup);
-    if constexpr (HANDOVER) load_stage(min(st + 2, nstages - 1), lmask);
+    if constexpr (RELOAD) {
+      if constexpr (D > 1) {
+        grp = grpn;
+        load_group(grpn, min((st + 2) / kGroup + 1, last / kGroup));
+      } else {
+        load_group(grp, (st + 2) / kGroup);
+      }
+    }
+    if constexpr (HANDOVER) load_stage(min(st + 1 + D, last), lmask, word_tag);
     WFrag w1;
     AFrag b0, b1;
     read_w(buf, 1, w1);
@@ -698,17 +728,19 @@ __global__ __launch_bounds__(Big::kThreads, 2) void rfq_gemm_large_kernel(RFQ_TI
                                                            phi, ksplit);
 }
 
-template <bool RES, bool ZBF16, bool SWIGLU, bool HRES, bool GK>
-__global__ __launch_bounds__(Mid::kThreads, 3) void rfq_gemm_mid_kernel(RFQ_TILE_ARGS) {
-  gemm_tile<Mid, RES, ZBF16, SWIGLU, HRES, false, false, GK>(qc, qs, rc, rs, wc, ws, M, N, K, z,
-                                                             so, phi, ksplit);
+template <class C, bool RES, bool ZBF16, bool SWIGLU, bool HRES, bool GK>
+__global__ __launch_bounds__(C::kThreads, C::kDepth > 1 ? 2 : 3) void rfq_gemm_mid_kernel(
+    RFQ_TILE_ARGS) {
+  gemm_tile<C, RES, ZBF16, SWIGLU, HRES, false, false, GK>(qc, qs, rc, rs, wc, ws, M, N, K, z, so,
+                                                           phi, ksplit);
 }
 
 // K split over several workgroups per 128 x 128 tile: fp32 partial products.
-template <bool RES, bool GK>
-__global__ __launch_bounds__(Mid::kThreads, 3) void rfq_gemm_split_kernel(RFQ_TILE_ARGS) {
-  gemm_tile<Mid, RES, false, false, false, false, true, GK>(qc, qs, rc, rs, wc, ws, M, N, K, z,
-                                                            so, phi, ksplit);
+template <class C, bool RES, bool GK>
+__global__ __launch_bounds__(C::kThreads, C::kDepth > 1 ? 2 : 3) void rfq_gemm_split_kernel(
+    RFQ_TILE_ARGS) {
+  gemm_tile<C, RES, false, false, false, false, true, GK>(qc, qs, rc, rs, wc, ws, M, N, K, z, so,
+                                                          phi, ksplit);
 }
 #undef RFQ_TILE_ARGS
 
@@ -763,7 +795,7 @@ hipError_t launch(const uint8_t *qc, const uint8_t *qs, const uint8_t *rc,
   if constexpr (std::is_same<C, Big>::value)
     kern = rfq_gemm_large_kernel<RES, ZBF16, SWIGLU, HRES, PHI, GK>;
   else
-    kern = rfq_gemm_mid_kernel<RES, ZBF16, SWIGLU, HRES, GK>;
+    kern = rfq_gemm_mid_kernel<C, RES, ZBF16, SWIGLU, HRES, GK>;
   // LDS: the two stage buffers, then (PHI) the rows of the indicator map.
   constexpr int kMaxBytes = L::kBytes + (PHI ? kPhiMapMaxBytes : 0);
   const int phi_bytes =
@@ -777,24 +809,28 @@ hipError_t launch(const uint8_t *qc, const uint8_t *qs, const uint8_t *rc,
   return hipGetLastError();
 }
 
+int64_t mid_tiles(int64_t M, int64_t N) {
+  return ((M + Mid::kBM - 1) / Mid::kBM) * ((N + Mid::kBN - 1) / Mid::kBN);
+}
+
 // K split into `parts` ranges of ksplit columns (a multiple of 512): the
 // partial products go to work[parts][M][N] (fp32), then one pass adds them.
-template <bool RES, bool GK = false>
+template <class C, bool RES, bool GK = false>
 hipError_t launch_split(const uint8_t *qc, const uint8_t *qs, const uint8_t *rc,
                         const uint8_t *rs, const uint8_t *wc, const uint8_t *ws, int64_t M,
                         int64_t N, int64_t K, void *z, bool z_bf16, float *work, int parts,
                         int64_t ksplit, hipStream_t stream) {
   if constexpr (!GK)
     if (K % (kStageK * kGroup))
-      return launch_split<RES, true>(qc, qs, rc, rs, wc, ws, M, N, K, z, z_bf16, work, parts,
-                                     ksplit, stream);
-  using L = Layout<Mid, RES>;
-  auto kern = rfq_gemm_split_kernel<RES, GK>;
+      return launch_split<C, RES, true>(qc, qs, rc, rs, wc, ws, M, N, K, z, z_bf16, work, parts,
+                                        ksplit, stream);
+  using L = Layout<C, RES>;
+  auto kern = rfq_gemm_split_kernel<C, RES, GK>;
   static std::atomic<bool> attr_done[kMaxDevices];
   hipError_t e = set_lds_limit(attr_done, reinterpret_cast<const void *>(kern), L::kBytes);
   if (e != hipSuccess) return e;
-  const int64_t ntiles = ((M + Mid::kBM - 1) / Mid::kBM) * ((N + Mid::kBN - 1) / Mid::kBN);
-  kern<<<dim3((unsigned)(ntiles * parts)), dim3(Mid::kThreads), L::kBytes, stream>>>(
+  const int64_t ntiles = mid_tiles(M, N);
+  kern<<<dim3((unsigned)(ntiles * parts)), dim3(C::kThreads), L::kBytes, stream>>>(
       qc, qs, rc, rs, wc, ws, M, N, K, work, SwigluOut{}, nullptr, ksplit);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   return launch_splitk_sum(work, parts, M * N, z, z_bf16, stream);
@@ -811,7 +847,7 @@ hipError_t launch_split(const uint8_t *qc, const uint8_t *qs, const uint8_t *rc,
 // 4096 25.7 -> 22.1 (2).  With K = 4096 and 192 tiles (129 rows x 12288)
 // two parts cost more than they save (21.3 -> 25.5 us).
 int splitk_default_parts(int64_t M, int64_t N, int64_t K) {
-  const int64_t tiles = ((M + Mid::kBM - 1) / Mid::kBM) * ((N + Mid::kBN - 1) / Mid::kBN);
+  const int64_t tiles = mid_tiles(M, N);
   if (tiles <= 128) return (int)std::min<int64_t>(8, 256 / tiles);
   if (tiles <= 192 && K >= 8192) return (int)std::min<int64_t>(4, 512 / tiles);
   return 1;
@@ -824,9 +860,18 @@ int splitk_default_parts(int64_t M, int64_t N, int64_t K) {
 // 4096 x 12288: 60-67 us against 108-117 us), 0.8-0.96 at 384-480 tiles,
 // 1.06-1.23 at 512-576.
 bool use_mid_tiles(int64_t M, int64_t N) {
-  const int64_t mid = ((M + Mid::kBM - 1) / Mid::kBM) * ((N + Mid::kBN - 1) / Mid::kBN);
-  return mid < 2 * 256;
+  return mid_tiles(M, N) < 2 * 256;
 }
+
+// MidDeep for `workgroups` 128 x 128 tiles (times parts of K): at most one
+// per CU.  Same bits.  Measured, one stage against two in registers: 192
+// tiles (129 and 256 rows x 12288 x 4096) 21.0 -> 18.3 and 23.5 -> 20.7 us,
+// 64 and 128 tiles (200 and 512 rows x 4096 x 12288) 60.4 -> 48.5 and 63.1 ->
+// 50.7, 256 tiles (1000 rows) 69.0 -> 64.4, split: 512 rows x 4096 x 12288
+// 44.3 -> 41.8, 300 x 4096 x 11008 37.3 -> 32.3; at 320 tiles (1000 rows x
+// 5000 x 2912), where three workgroups share a CU only without it, 29.7 ->
+// 33.1, at 384 and 480 no gain.  Four stages gave no more than two.
+bool use_deep_tiles(int64_t workgroups) { return workgroups <= 256; }
 
 }  // namespace
 
@@ -868,11 +913,15 @@ hipError_t launch_gemm_large_split(const uint8_t *q_codes, const uint8_t *q_scal
   if (plan.parts < 2)
     return launch_gemm_large(q_codes, q_scales, r_codes, r_scales, w_codes, w_scales, M, N, K,
                              z, z_bf16, stream);
-  if (r_codes)
-    return launch_split<true>(q_codes, q_scales, r_codes, r_scales, w_codes, w_scales, M, N, K,
-                              z, z_bf16, work, plan.parts, plan.ksplit, stream);
-  return launch_split<false>(q_codes, q_scales, r_codes, r_scales, w_codes, w_scales, M, N, K, z,
-                             z_bf16, work, plan.parts, plan.ksplit, stream);
+  auto go = [&](auto tile) {
+    using C = decltype(tile);
+    if (r_codes)
+      return launch_split<C, true>(q_codes, q_scales, r_codes, r_scales, w_codes, w_scales, M, N,
+                                   K, z, z_bf16, work, plan.parts, plan.ksplit, stream);
+    return launch_split<C, false>(q_codes, q_scales, r_codes, r_scales, w_codes, w_scales, M, N, K,
+                                  z, z_bf16, work, plan.parts, plan.ksplit, stream);
+  };
+  return use_deep_tiles(mid_tiles(M, N) * plan.parts) ? go(MidDeep{}) : go(Mid{});
 }
 
 bool large_tiles_beat_few_rows(int64_t M, int64_t N) {
@@ -926,13 +975,15 @@ hipError_t launch_gemm_large(const uint8_t *q_codes, const uint8_t *q_scales,
       return launch<C, false, true>(qc, qs, rc, rs, w_codes, w_scales, rows, N, K, zr, stream);
     return launch<C, false, false>(qc, qs, rc, rs, w_codes, w_scales, rows, N, K, zr, stream);
   };
-  if (use_mid_tiles(M, N)) return go(Mid{}, 0, M);
+  if (use_mid_tiles(M, N))
+    return use_deep_tiles(mid_tiles(M, N)) ? go(MidDeep{}, 0, M) : go(Mid{}, 0, M);
   const int64_t big_rows = std::min<int64_t>(big_tile_rows(M, N) * Big::kBM, M);
   const hipError_t e = go(Big{}, 0, big_rows);
   if (e != hipSuccess || big_rows == M) return e;
   // Both tile shapes accumulate every output in the same order, so the
   // peeled rows carry the bits the 256 x 256 tiles would give them.
-  return go(Mid{}, big_rows, M - big_rows);
+  return use_deep_tiles(mid_tiles(M - big_rows, N)) ? go(MidDeep{}, big_rows, M - big_rows)
+                                                    : go(Mid{}, big_rows, M - big_rows);
 }
 
 hipError_t launch_gemm_large_phi(const uint8_t *q_codes, const uint8_t *q_scales,
@@ -972,7 +1023,8 @@ hipError_t launch_gemm_swiglu(const uint8_t *q_codes, const uint8_t *q_scales,
     return launch<C, false, true, true, false>(q_codes, q_scales, r_codes, r_scales, wgu_codes,
                                                wgu_scales, M, N, K, nullptr, stream, so);
   };
-  return use_mid_tiles(M, N) ? go(Mid{}) : go(Big{});
+  if (!use_mid_tiles(M, N)) return go(Big{});
+  return use_deep_tiles(mid_tiles(M, N)) ? go(MidDeep{}) : go(Mid{});
 }
 
 }  // namespace rfq

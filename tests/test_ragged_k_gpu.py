@@ -23,6 +23,8 @@ SHAPES = [
     (7, 12300, 672),         # 64 weight rows per workgroup
     (20, 8200, 736),         # 32 weight rows per workgroup
     (129, 257, 96),          # 128-wide tiles: one short stage
+    (130, 140, 256),         # two and three stages (the loads' whole lead)
+    (130, 140, 384),
     (200, 328, 672),         # 21 blocks: 6 stages
     (300, 130, 896),         # 28 blocks: 7 whole stages
     (385, 260, 1120),        # 35 blocks: 9 stages
