@@ -345,12 +345,29 @@ static bool few_rows_beat_split(int64_t M, int64_t N, int64_t K) {
   return M < min_rows;
 }
 
+// Where a split does not pay: each part is too short against the partial
+// sums' pass (a launch of its own, 3 to 5 us).  Measured unsplit / split, bf16
+// Z, 40 to 512 rows: K = 1024 3.8 / 7.6 (40 x 1024) to 7.1 / 20.1 (512 x 4096),
+// K = 2048 5.4 / 8.1 (40 x 1024) to 10.6 / 21.9 (512 x 4096), K = 3072 7.7 /
+// 10.9 (40 x 4096) to 14.2 / 22.9 (512 x 4096), K = 4096 10.2 / 12.2 (40 x
+// 4096), 17.3 / 21.6 (256 x 4096).  At K = 4096 and 65-192 rows it depends on N
+// (19.6 / 15.1 at 100 x 3072, 14.0 / 17.4 at 100 x 4096), and 65-128 rows at
+// N = 8192 gain from K = 2048 on (12.0 / 11.4): split there as at longer K.
+// Narrow outputs (below N = 512) have too few workgroups unsplit (160 x 300
+// x 2560: 12.9 / 10.4).
+static bool too_short_to_split(int64_t M, int64_t N, int64_t K) {
+  if (N < 512 || K > 4096) return false;
+  if (N <= 4096) return K <= 3072 || M <= 64 || M > 192;
+  return K <= 2048 && (M <= 64 || M > 128);
+}
+
 int64_t gemm_split_bytes(int64_t M, int64_t N, int64_t K) {
   if (M <= 0 || N <= 0 || K < 32 || (K % 32) != 0) return 0;
   if (few_rows_chosen(M, N) && few_rows_beat_split(M, N, K)) {
     const int parts = skinny_split_parts(M, N, K);
     return parts > 1 ? int64_t(parts) * M * N * 4 : 0;
   }
+  if (too_short_to_split(M, N, K)) return 0;
   const SplitPlan p = splitk_plan(M, N, K);
   return p.parts > 1 ? p.work_bytes : 0;
 }
@@ -362,7 +379,7 @@ hipError_t launch_gemm(const uint8_t *q_codes, const uint8_t *q_scales,
                        hipStream_t stream, float *work, int64_t work_bytes) {
   const bool large = gemm_large_applies(q_scales, r_scales, w_scales, M, N, K);
   SplitPlan plan{1, K, 0};
-  if (large && work) {
+  if (large && work && !too_short_to_split(M, N, K)) {
     plan = splitk_plan(M, N, K);
     if (plan.work_bytes > work_bytes) plan = SplitPlan{1, K, 0};
   }
