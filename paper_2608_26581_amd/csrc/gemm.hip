@@ -416,7 +416,18 @@ hipError_t launch_gemm_phi(const uint8_t *q_codes, const uint8_t *q_scales,
                            const uint8_t *w_codes, const uint8_t *w_scales, const uint8_t *phi,
                            int64_t M, int64_t N, int64_t K, void *z, bool z_bf16,
                            hipStream_t stream) {
-  if (gemm_large_applies(q_scales, r_scales, w_scales, M, N, K))
+  // The kernels and their ranges of rows are those of the product without a
+  // map.  Measured with 75-100% of the tiles on (bf16 Z), 256 x 256 tiles at
+  // every M against this: 1 row x 12288 x 4096 33.7 -> 8.0 us (without a map
+  // 7.8), 16 x 4096 x 12288 91.7 -> 12.9 (12.9), 64 x 4096 x 4096 34.8 -> 12.9
+  // (12.8), 200 x 12288 x 4096 43.6 -> 22.4 (18.9), 512 x 4096 x 12288 119.3 ->
+  // 55.9 (50.5), 4096 x 5120 x 13824 (last tile rows 128-wide) 321 -> 296.
+  const bool large = gemm_large_applies(q_scales, r_scales, w_scales, M, N, K);
+  if (gemm_skinny_applies(q_scales, r_scales, w_scales, M, N, K) &&
+      !(large && large_tiles_beat_few_rows(M, N)))
+    return launch_gemm_skinny_phi(q_codes, q_scales, r_codes, r_scales, w_codes, w_scales, phi, M,
+                                  N, K, z, z_bf16, stream);
+  if (large)
     return launch_gemm_large_phi(q_codes, q_scales, r_codes, r_scales, w_codes, w_scales, phi, M,
                                  N, K, z, z_bf16, stream);
   constexpr int BM = 128, BN = 128;

@@ -268,7 +268,7 @@ __device__ __forceinline__ void swiglu_epilogue(const v16f (&acc)[C::kFM][C::kFN
 }
 
 // Fallback-indicator map: one byte per tile of kPhiRows activation rows by
-// kPhiK reduction columns (a wave's rows by two stages); 256 x 256 tiles only.
+// kPhiK reduction columns (a wave's rows by two stages).
 constexpr int kPhiRows = 64, kPhiK = 256;
 // LDS reserved for the map rows of a workgroup (K up to 2^20).
 constexpr int kPhiMapMaxBytes = Big::kWaveRows * ((1 << 20) / kPhiK);
@@ -293,7 +293,7 @@ __device__ __forceinline__ void gemm_tile(
     const uint8_t *__restrict__ wc, const uint8_t *__restrict__ ws,
     int64_t M, int64_t N, int64_t K, void *__restrict__ z, const SwigluOut so,
     const uint8_t *__restrict__ phi, int64_t ksplit) {
-  static_assert(!PHI || std::is_same<C, Big>::value, "fallback-indicator maps use 256 x 256 tiles");
+  static_assert(!PHI || C::kTM == kPhiRows, "a wave's rows are one indicator row");
   static_assert(!SPLIT || (!ZBF16 && !SWIGLU && !PHI), "split partials are fp32 products");
   using L = Layout<C, RES>;
   constexpr int kBM = C::kBM, kBN = C::kBN, kTM = C::kTM, kTN = C::kTN;
@@ -502,8 +502,8 @@ __device__ __forceinline__ void gemm_tile(
   using Rl = std::integral_constant<bool, true>;
   using NoRl = std::integral_constant<bool, false>;
 
-  // The fallback-indicator bytes of this workgroup's four wave rows, copied
-  // to LDS behind the stage buffers, four per reduction tile (one 32-bit
+  // The fallback-indicator bytes of this workgroup's four (two) wave rows,
+  // copied to LDS behind the stage buffers, four (two) per reduction tile (one
   // word per tile; the prologue's barrier publishes them).
   const int pcols = (int)((K + kPhiK - 1) / kPhiK);
   uint8_t *phi_lds = smem + L::kBytes;
@@ -515,17 +515,20 @@ __device__ __forceinline__ void gemm_tile(
     }
   }
   const int wm_u = __builtin_amdgcn_readfirstlane(wm);
-  // This thread's residual row blocks (u = kBM / kRPL + b) belong to wave
-  // rows lw and lw + 2, b = 0, 1: rows 16 wave + 128 b of the residual tile.
+  // This thread's residual row block b (u = kBM / kRPL + b, rows 16 wave +
+  // kRPL b of the residual tile) belongs to wave row lw + kRPL / 64 b.
   const int lw = __builtin_amdgcn_readfirstlane(wave >> 2);
   auto phi_word = [&](int st) -> uint32_t {
+    using Word = std::conditional_t<kWaveRows == 4, uint32_t, uint16_t>;
     return __builtin_amdgcn_readfirstlane(
-        *reinterpret_cast<const uint32_t *>(phi_lds + kWaveRows * (st / 2)));
+        (uint32_t)*reinterpret_cast<const Word *>(phi_lds + kWaveRows * (st / 2)));
   };
   // Bit b: the residual row block b of stage st is needed.
   auto res_mask = [&](int st) -> int {
     const uint32_t w = phi_word(st);
-    return (((w >> (8 * lw)) & 0xFFu) ? 1 : 0) | (((w >> (8 * (lw + 2))) & 0xFFu) ? 2 : 0);
+    constexpr int kStep = kRPL / kPhiRows;
+    static_assert(kBM / kRPL == 2, "two residual row blocks per thread");
+    return (((w >> (8 * lw)) & 0xFFu) ? 1 : 0) | (((w >> (8 * (lw + kStep))) & 0xFFu) ? 2 : 0);
   };
   // ---- prologue: stage 0 into buffer 0, stage 1 in registers.
   if constexpr (PHI) __syncthreads();   // the indicator words
@@ -728,10 +731,10 @@ __global__ __launch_bounds__(Big::kThreads, 2) void rfq_gemm_large_kernel(RFQ_TI
                                                            phi, ksplit);
 }
 
-template <class C, bool RES, bool ZBF16, bool SWIGLU, bool HRES, bool GK>
+template <class C, bool RES, bool ZBF16, bool SWIGLU, bool HRES, bool PHI, bool GK>
 __global__ __launch_bounds__(C::kThreads, C::kDepth > 1 ? 2 : 3) void rfq_gemm_mid_kernel(
     RFQ_TILE_ARGS) {
-  gemm_tile<C, RES, ZBF16, SWIGLU, HRES, false, false, GK>(qc, qs, rc, rs, wc, ws, M, N, K, z, so,
+  gemm_tile<C, RES, ZBF16, SWIGLU, HRES, PHI, false, GK>(qc, qs, rc, rs, wc, ws, M, N, K, z, so,
                                                            phi, ksplit);
 }
 
@@ -795,7 +798,7 @@ hipError_t launch(const uint8_t *qc, const uint8_t *qs, const uint8_t *rc,
   if constexpr (std::is_same<C, Big>::value)
     kern = rfq_gemm_large_kernel<RES, ZBF16, SWIGLU, HRES, PHI, GK>;
   else
-    kern = rfq_gemm_mid_kernel<C, RES, ZBF16, SWIGLU, HRES, GK>;
+    kern = rfq_gemm_mid_kernel<C, RES, ZBF16, SWIGLU, HRES, PHI, GK>;
   // LDS: the two stage buffers, then (PHI) the rows of the indicator map.
   constexpr int kMaxBytes = L::kBytes + (PHI ? kPhiMapMaxBytes : 0);
   const int phi_bytes =
@@ -954,12 +957,26 @@ static int64_t big_tile_rows(int64_t M, int64_t N) {
   return rows > 0 ? rows : ntm;
 }
 
+// rows -> tile shape, for the product with or without a map.
+template <class Go>
+static hipError_t on_tiles(int64_t M, int64_t N, Go go) {
+  if (use_mid_tiles(M, N))
+    return use_deep_tiles(mid_tiles(M, N)) ? go(MidDeep{}, 0, M) : go(Mid{}, 0, M);
+  const int64_t big_rows = std::min<int64_t>(big_tile_rows(M, N) * Big::kBM, M);
+  const hipError_t e = go(Big{}, 0, big_rows);
+  if (e != hipSuccess || big_rows == M) return e;
+  // Both tile shapes accumulate every output in the same order, so the
+  // peeled rows carry the bits the 256 x 256 tiles would give them.
+  return use_deep_tiles(mid_tiles(M - big_rows, N)) ? go(MidDeep{}, big_rows, M - big_rows)
+                                                    : go(Mid{}, big_rows, M - big_rows);
+}
+
 hipError_t launch_gemm_large(const uint8_t *q_codes, const uint8_t *q_scales,
                              const uint8_t *r_codes, const uint8_t *r_scales,
                              const uint8_t *w_codes, const uint8_t *w_scales,
                              int64_t M, int64_t N, int64_t K, void *z, bool z_bf16,
                              hipStream_t stream) {
-  auto go = [&](auto tile, int64_t row0, int64_t rows) {
+  return on_tiles(M, N, [&](auto tile, int64_t row0, int64_t rows) {
     using C = decltype(tile);
     // Activation rows [row0, row0 + rows) and the same rows of Z.
     const uint8_t *qc = q_codes + row0 * (K / 2), *qs = q_scales + row0 * (K / 32);
@@ -974,16 +991,7 @@ hipError_t launch_gemm_large(const uint8_t *q_codes, const uint8_t *q_scales,
     if (z_bf16)
       return launch<C, false, true>(qc, qs, rc, rs, w_codes, w_scales, rows, N, K, zr, stream);
     return launch<C, false, false>(qc, qs, rc, rs, w_codes, w_scales, rows, N, K, zr, stream);
-  };
-  if (use_mid_tiles(M, N))
-    return use_deep_tiles(mid_tiles(M, N)) ? go(MidDeep{}, 0, M) : go(Mid{}, 0, M);
-  const int64_t big_rows = std::min<int64_t>(big_tile_rows(M, N) * Big::kBM, M);
-  const hipError_t e = go(Big{}, 0, big_rows);
-  if (e != hipSuccess || big_rows == M) return e;
-  // Both tile shapes accumulate every output in the same order, so the
-  // peeled rows carry the bits the 256 x 256 tiles would give them.
-  return use_deep_tiles(mid_tiles(M - big_rows, N)) ? go(MidDeep{}, big_rows, M - big_rows)
-                                                    : go(Mid{}, big_rows, M - big_rows);
+  });
 }
 
 hipError_t launch_gemm_large_phi(const uint8_t *q_codes, const uint8_t *q_scales,
@@ -991,13 +999,20 @@ hipError_t launch_gemm_large_phi(const uint8_t *q_codes, const uint8_t *q_scales
                                  const uint8_t *w_codes, const uint8_t *w_scales,
                                  const uint8_t *phi, int64_t M, int64_t N, int64_t K, void *z,
                                  bool z_bf16, hipStream_t stream) {
-  if (z_bf16)
-    return launch<Big, true, true, false, false, true>(q_codes, q_scales, r_codes, r_scales,
-                                                       w_codes, w_scales, M, N, K, z, stream,
-                                                       SwigluOut{}, phi);
-  return launch<Big, true, false, false, false, true>(q_codes, q_scales, r_codes, r_scales,
-                                                      w_codes, w_scales, M, N, K, z, stream,
-                                                      SwigluOut{}, phi);
+  return on_tiles(M, N, [&](auto tile, int64_t row0, int64_t rows) {
+    using C = decltype(tile);
+    // row0 is a multiple of 256: whole rows of the map.
+    const int64_t co = row0 * (K / 2), so = row0 * (K / 32);
+    const uint8_t *pr = phi + row0 / kPhiRows * ((K + kPhiK - 1) / kPhiK);
+    void *zr = static_cast<uint8_t *>(z) + row0 * N * (z_bf16 ? 2 : 4);
+    if (z_bf16)
+      return launch<C, true, true, false, false, true>(q_codes + co, q_scales + so, r_codes + co,
+                                                       r_scales + so, w_codes, w_scales, rows, N,
+                                                       K, zr, stream, SwigluOut{}, pr);
+    return launch<C, true, false, false, false, true>(q_codes + co, q_scales + so, r_codes + co,
+                                                      r_scales + so, w_codes, w_scales, rows, N, K,
+                                                      zr, stream, SwigluOut{}, pr);
+  });
 }
 
 hipError_t launch_gemm_swiglu(const uint8_t *q_codes, const uint8_t *q_scales,

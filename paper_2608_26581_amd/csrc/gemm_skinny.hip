@@ -185,7 +185,7 @@ __device__ __forceinline__ void reduce_store(v4f (&partial)[kSkThreads / 64][64]
 // the order z = 0, 1, ...  With one part the ranges and the output are those
 // of the unsplit product.
 template <int F>
-struct WPair { WGroup f[F]; };
+struct WPair { WGroup f[F]; uint32_t phi[2]; };
 
 // GK: any K a multiple of 32 (without it a multiple of 512).  The last group
 // may then hold fewer than 16 blocks: W's codes past K load as zeros (so the
@@ -193,12 +193,19 @@ struct WPair { WGroup f[F]; };
 // bytes past K are masked to 0 (a neighbouring row's could be NaN).  A row's
 // scale bytes start at any byte: the five aligned dwords that hold a group's
 // 16 are loaded and shifted into place.
-template <bool RES, bool ZBF16, int S, int F, bool GK>
-__global__ __launch_bounds__(kSkThreads, F == 1 ? 3 : (F == 2 ? 2 : 1)) void rfq_gemm_skinny_kernel(
+//
+// PHI: a fallback-indicator map, one byte per 64 rows (all the slices of a
+// workgroup) by 256 columns (two k-steps): the residual MFMAs of k-steps whose
+// byte is 0 are skipped.  The kernel is bound by W's codes, so this takes the
+// time of the product without a map.
+template <bool RES, bool ZBF16, int S, int F, bool GK, bool PHI>
+__global__ __launch_bounds__(kSkThreads, F == 1 && !(PHI && GK && S == 4) ? 3 : (F <= 2 ? 2 : 1)) void
+rfq_gemm_skinny_kernel(
     const uint8_t *__restrict__ qc, const uint8_t *__restrict__ qs,
     const uint8_t *__restrict__ rc, const uint8_t *__restrict__ rs,
     const uint8_t *__restrict__ wc, const uint8_t *__restrict__ ws, int64_t M, int64_t N,
-    int64_t K, void *__restrict__ z) {
+    int64_t K, void *__restrict__ z, const uint8_t *__restrict__ phi) {
+  static_assert(!PHI || RES, "a map switches the residual");
   __shared__ v4f partial[kSkThreads / 64][F * S][64];
 
   const int lane = threadIdx.x & 63;
@@ -240,6 +247,8 @@ __global__ __launch_bounds__(kSkThreads, F == 1 ? 3 : (F == 2 ? 2 : 1)) void rfq
     }
     return o;
   };
+  const int64_t pcols = (K + 255) / 256;
+  const __amdgpu_buffer_rsrc_t rphi = rsrc(PHI ? phi + m0 / 64 * pcols : nullptr, PHI ? pcols : 0);
   uint32_t w_off[F], ws_off[F];
 #pragma unroll
   for (int f = 0; f < F; ++f) {
@@ -257,6 +266,11 @@ __global__ __launch_bounds__(kSkThreads, F == 1 ? 3 : (F == 2 ? 2 : 1)) void rfq
             rwc, past ? 0x80000000u : w_off[f], gi * (kSkGroupK / 2) + 64 * j, 0);
       }
       load_scales(rws, ws_off[f], gi, w.f[f].s, w.f[f].s4);
+    }
+    if constexpr (PHI) {   // past the map's row: columns past K, whose W codes are zeros
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        w.phi[h] = __builtin_amdgcn_raw_buffer_load_b8(rphi, 0, 2 * gi + h, 0);
     }
   };
 
@@ -293,6 +307,24 @@ __global__ __launch_bounds__(kSkThreads, F == 1 ? 3 : (F == 2 ? 2 : 1)) void rfq
     u32x4 wsc[F];
 #pragma unroll
     for (int f = 0; f < F; ++f) wsc[f] = place_scales(w.f[f].s, w.f[f].s4, ws_off[f], gi);
+    if constexpr (PHI) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const bool on = __builtin_amdgcn_readfirstlane(w.phi[h] & 0xFFu) != 0;
+#pragma unroll
+        for (int j = 2 * h; j < 2 * h + 2; ++j) {
+#pragma unroll
+          for (int f = 0; f < F; ++f)
+            a[f] = mma16(w.f[f].c[j], scale_of(wsc[f], j, g), xg.q[j], scale_of(qsc, j, g), a[f]);
+          if (on) {
+#pragma unroll
+            for (int f = 0; f < F; ++f)
+              a[f] = mma16(w.f[f].c[j], scale_of(wsc[f], j, g), xg.r[j], scale_of(rsc, j, g), a[f]);
+          }
+        }
+      }
+      return;
+    }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
 #pragma unroll
@@ -552,18 +584,18 @@ __global__ __launch_bounds__(kSkThreads, (XF32 || kStFrags > 1) ? 1 : 2) void rf
   }
 }
 
-template <bool RES, bool ZBF16, int S, int F>
+template <bool RES, bool ZBF16, bool PHI, int S, int F>
 hipError_t launch_sk_s(const uint8_t *qc, const uint8_t *qs, const uint8_t *rc, const uint8_t *rs,
                        const uint8_t *wc, const uint8_t *ws, int64_t M, int64_t N, int64_t K,
-                       void *z, int parts, hipStream_t stream) {
+                       void *z, const uint8_t *phi, int parts, hipStream_t stream) {
   const dim3 grid((unsigned)((N + F * kSkRows - 1) / (F * kSkRows)),
                   (unsigned)((M + S * kSkRows - 1) / (S * kSkRows)), (unsigned)parts);
   if (K % kSkGroupK)
-    rfq_gemm_skinny_kernel<RES, ZBF16, S, F, true><<<grid, dim3(kSkThreads), 0, stream>>>(
-        qc, qs, rc, rs, wc, ws, M, N, K, z);
+    rfq_gemm_skinny_kernel<RES, ZBF16, S, F, true, PHI><<<grid, dim3(kSkThreads), 0, stream>>>(
+        qc, qs, rc, rs, wc, ws, M, N, K, z, phi);
   else
-    rfq_gemm_skinny_kernel<RES, ZBF16, S, F, false><<<grid, dim3(kSkThreads), 0, stream>>>(
-        qc, qs, rc, rs, wc, ws, M, N, K, z);
+    rfq_gemm_skinny_kernel<RES, ZBF16, S, F, false, PHI><<<grid, dim3(kSkThreads), 0, stream>>>(
+        qc, qs, rc, rs, wc, ws, M, N, K, z, phi);
   return hipGetLastError();
 }
 
@@ -594,11 +626,12 @@ int64_t sk_workgroups(int64_t M, int64_t N) {
   return ((N + F * kSkRows - 1) / (F * kSkRows)) * ((M + S * kSkRows - 1) / (S * kSkRows));
 }
 
-template <bool RES, bool ZBF16>
+template <bool RES, bool ZBF16, bool PHI = false>
 hipError_t launch_sk(const uint8_t *qc, const uint8_t *qs, const uint8_t *rc, const uint8_t *rs,
                      const uint8_t *wc, const uint8_t *ws, int64_t M, int64_t N, int64_t K,
-                     void *z, hipStream_t stream, int parts = 1) {
-#define RFQ_SK(S, F) launch_sk_s<RES, ZBF16, S, F>(qc, qs, rc, rs, wc, ws, M, N, K, z, parts, stream)
+                     void *z, hipStream_t stream, int parts = 1, const uint8_t *phi = nullptr) {
+#define RFQ_SK(S, F) \
+  launch_sk_s<RES, ZBF16, PHI, S, F>(qc, qs, rc, rs, wc, ws, M, N, K, z, phi, parts, stream)
   const int S = sk_slices(M), F = sk_fragments(M, N);
   if (S == 1) return F == 4 ? RFQ_SK(1, 4) : (F == 2 ? RFQ_SK(1, 2) : RFQ_SK(1, 1));
   if (S == 2) return F == 4 ? RFQ_SK(2, 4) : (F == 2 ? RFQ_SK(2, 2) : RFQ_SK(2, 1));
@@ -686,6 +719,18 @@ hipError_t launch_gemm_skinny(const uint8_t *q_codes, const uint8_t *q_scales,
   if (z_bf16)
     return launch_sk<false, true>(q_codes, q_scales, nullptr, nullptr, w_codes, w_scales, M, N, K, z, stream);
   return launch_sk<false, false>(q_codes, q_scales, nullptr, nullptr, w_codes, w_scales, M, N, K, z, stream);
+}
+
+hipError_t launch_gemm_skinny_phi(const uint8_t *q_codes, const uint8_t *q_scales,
+                                  const uint8_t *r_codes, const uint8_t *r_scales,
+                                  const uint8_t *w_codes, const uint8_t *w_scales,
+                                  const uint8_t *phi, int64_t M, int64_t N, int64_t K, void *z,
+                                  bool z_bf16, hipStream_t stream) {
+  if (z_bf16)
+    return launch_sk<true, true, true>(q_codes, q_scales, r_codes, r_scales, w_codes, w_scales, M,
+                                       N, K, z, stream, 1, phi);
+  return launch_sk<true, false, true>(q_codes, q_scales, r_codes, r_scales, w_codes, w_scales, M,
+                                      N, K, z, stream, 1, phi);
 }
 
 hipError_t launch_gemm_skinny_split(const uint8_t *q_codes, const uint8_t *q_scales,

@@ -126,6 +126,12 @@ hipError_t launch_gemm_skinny(const uint8_t *q_codes, const uint8_t *q_scales,
                               const uint8_t *r_codes, const uint8_t *r_scales,
                               const uint8_t *w_codes, const uint8_t *w_scales, int64_t M,
                               int64_t N, int64_t K, void *z, bool z_bf16, hipStream_t stream);
+// The same with a fallback-indicator map (residual operand required).
+hipError_t launch_gemm_skinny_phi(const uint8_t *q_codes, const uint8_t *q_scales,
+                                  const uint8_t *r_codes, const uint8_t *r_scales,
+                                  const uint8_t *w_codes, const uint8_t *w_scales,
+                                  const uint8_t *phi, int64_t M, int64_t N, int64_t K, void *z,
+                                  bool z_bf16, hipStream_t stream);
 // Whether the few-row kernel's grid for this shape holds between one and two
 // workgroups per CU (so some CUs run two and the rest one).
 bool skinny_grid_uneven(int64_t M, int64_t N);

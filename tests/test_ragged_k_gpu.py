@@ -108,3 +108,29 @@ def test_unaligned_scale_tensors(orc, M, N, K):
     print("unaligned scales: M=%d N=%d K=%d" % (M, N, K), flush=True)
     _check(orc, rfq.rfq_gemm(q[0], shifted(q[1]), q[2], shifted(q[3]), w[0], shifted(w[1])), q, w,
            "unaligned scales")
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 70, 512), (16, 300, 1312), (20, 8200, 800), (40, 130, 2048),
+                                   (100, 260, 992), (7, 12300, 1024), (100, 12300, 1056),
+                                   (200, 130, 2336), (700, 2900, 1120), (2900, 2900, 608)])
+def test_random_maps(orc, M, N, K):
+    """Maps on the few-row, 128-wide and 256-wide kernels (the last two rows of
+    256-wide tiles run 128-wide ones): random, one all-ones column and row."""
+    q, w = _operands(M, N, K, M + N)
+    rng = np.random.default_rng(N)
+    phi = (rng.random(((M + 63) // 64, (K + 255) // 256)) < 0.5).astype(np.uint8) * 3
+    phi[:, -1] = 1
+    phi[-1] = 1
+    rows = np.arange(M) if M <= 200 else np.unique(np.concatenate(
+        [np.arange(64 * ((M - 1) // 64) - 2, M), rng.integers(0, M, 24)]))
+    print("maps: M=%d N=%d K=%d" % (M, N, K), flush=True)
+    # The oracle on the sampled rows: their map rows repeated for 64-row tiles.
+    hq = [host(t) for t in q]
+    for dt in (torch.float32, torch.bfloat16):
+        z = rfq.rfq_gemm_phi(*q, *w, dev(phi), out_dtype=dt)
+        zh = host_bf16_as_f32(z) if dt == torch.bfloat16 else host(z)
+        for p in range(phi.shape[0]):
+            r = rows[rows // 64 == p]
+            if len(r):
+                zr, bound = orc.gemm_phi(*[t[r] for t in hq], host(w[0]), host(w[1]), phi[p:p + 1])
+                assert_gemm_close(zh[r], zr, bound, dt == torch.bfloat16, "map row %d" % p)
