@@ -281,8 +281,11 @@ struct HSmem {
   static constexpr int kBufBytes = kRows * kRowBytes;
   static constexpr int kBytes = 2 * kBufBytes;
   // Producer waves: each lane decodes two half-block rows per step (8 waves,
-  // two per SIMD, with the residual and BN = 256).
-  static constexpr int kProducers = kRows / 64;
+  // two per SIMD, with the residual and BN = 256), with BN = 128 one (12 waves,
+  // three per SIMD, where 6 left two SIMDs with twice the decode of the others:
+  // 512 rows x 12288 x 4096 170.9 -> 163.8 us, plain 300 x 5120 x 13824 199.3
+  // -> 161.1).
+  static constexpr int kProducers = kRows / (BN == 128 ? 32 : 64);
   static constexpr int kThreads = (kProducers + 4) * 64;
   static constexpr int kTN = BN / 2, kFN = kTN / 32;
 };
@@ -296,36 +299,40 @@ __device__ __forceinline__ int hswz(int row, int chunk) {
   return row * kRowBytes + 16 * (chunk ^ ((row >> 1) & 7));
 }
 
-// a & m, opaque to the optimizer, so that the byte conversions below stay
-// single v_cvt_f32_ubyte{0..3} instructions instead of a bit-field extract
-// per element followed by a conversion.
-__device__ __forceinline__ uint32_t and_opaque(uint32_t a, uint32_t m) {
-  uint32_t r;
-  asm("v_and_b32 %0, %1, %2" : "=v"(r) : "s"(m), "v"(a));
-  return r;
+// What the four code words of one half (32 elements) of a block share: the
+// unit of k = 1 at exponent 0 times 2^9 (as fp32 bits) and the micro-exponent
+// bits of the half, E1_8 bits 0-3 and E1_16 bits 0-7.
+struct HalfUnits {
+  uint32_t base, e8, e16;
+};
+__device__ __forceinline__ HalfUnits half_units(uint32_t meta, int half) {
+  const float base = (float)(4 + (meta & 3)) * pow2((int)((meta >> 2) & 63) - 43);
+  return HalfUnits{__float_as_uint(base), meta >> (8 + 4 * half), meta >> (16 + 8 * half)};
 }
 
-// bf16 pairs of the 8 elements of code word w (8-element group g of a block
-// with metadata meta): element 2p in the low half of pair p.
-__device__ __forceinline__ u32x4 decode8_bf16(uint32_t w, uint32_t meta, int g) {
-  float ua, ub;
-  group_units(meta, g, ua, ub);
-  const uint32_t lo = and_opaque(w, 0x07070707u), hi = and_opaque(w >> 4, 0x07070707u);
-  const uint32_t w4 = w << 4;
-  uint32_t p[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const float u = q < 2 ? ua : ub;
-    const float f0 = (float)((lo >> (8 * q)) & 0xFFu) * u;   // element 2q (exact)
-    const float f1 = (float)((hi >> (8 * q)) & 0xFFu) * u;   // element 2q + 1
-    const uint32_t pair = __builtin_amdgcn_perm(__float_as_uint(f1), __float_as_uint(f0),
-                                                0x07060302u);
-    // Sign bits: bit 7 of byte q of w4 (element 2q) to bit 15, bit 7 of
-    // byte q of w (element 2q + 1) to bit 31.
-    const uint32_t sgn = __builtin_amdgcn_perm(w, w4, 0x000C000Cu | (q << 8) | ((4 + q) << 24));
-    p[q] = pair | (sgn & 0x80008000u);
-  }
-  return u32x4{p[0], p[1], p[2], p[3]};
+// bf16 pairs of the 8 elements of code word w, the q-th of its half: element
+// 2p in the low half of pair p.  As an FP8 E4M3 byte, sign << 7 | k is the
+// subnormal +-k 2^-9, so the hardware's FP8 conversion gives two signed
+// elements an instruction; the unit carries the 2^9.  About 3.7 VALU
+// instructions per element, against 5.3 with a byte conversion per element and
+// the signs inserted into the pairs (64 rows x 4096 x 12288, split: 43.3 -> 39.7
+// us; 4 rows x 12288 x 4096 17.7 -> 16.6; same bits).
+__device__ __forceinline__ u32x4 decode8_bf16(uint32_t w, const HalfUnits &u, int q) {
+  const uint32_t lo = (w & 0x07070707u) | ((w << 4) & 0x80808080u);   // elements 0, 2, 4, 6
+  const uint32_t hi = ((w >> 4) & 0x07070707u) | (w & 0x80808080u);   // elements 1, 3, 5, 7
+  const uint32_t b8 = u.base + (((u.e8 >> q) & 1u) << 23);
+  const float ua = __uint_as_float(b8 + (((u.e16 >> (2 * q)) & 1u) << 23));
+  const float ub = __uint_as_float(b8 + (((u.e16 >> (2 * q + 1)) & 1u) << 23));
+  const f32x2_t a = __builtin_amdgcn_cvt_pk_f32_fp8((int)lo, false);
+  const f32x2_t b = __builtin_amdgcn_cvt_pk_f32_fp8((int)hi, false);
+  const f32x2_t c = __builtin_amdgcn_cvt_pk_f32_fp8((int)lo, true);
+  const f32x2_t d = __builtin_amdgcn_cvt_pk_f32_fp8((int)hi, true);
+  // Exact products; the pair keeps their upper halves.
+  auto pair = [](float x, float y) {
+    return __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u);
+  };
+  return u32x4{pair(a[0] * ua, b[0] * ua), pair(a[1] * ua, b[1] * ua), pair(c[0] * ub, d[0] * ub),
+               pair(c[1] * ub, d[1] * ub)};
 }
 
 // WBF16: the weights come as bf16 values wv[N][K] (for example HiF4 weights
@@ -399,26 +406,27 @@ __global__ __launch_bounds__((HSmem<RES, BN>::kThreads)) void hif4_gemm_kernel(
     }
     const int h = pt & 1;
     // Codes (or bf16 weight values: four 16-byte pieces per item) of step
-    // s + 1 are loaded while step s is decoded.  Whether an item is a weight
-    // row is uniform over a wave.
+    // s + 1 are loaded in place once step s is decoded (a second set of
+    // registers copied over after the barrier: 300 rows x 5120 x 13824, split,
+    // 189.5 us against 163.7; two or four steps ahead: no more).  Whether an
+    // item is a weight row is uniform over a wave.
     constexpr int kV = WBF16 ? 4 : 1;
-    u32x4 cw[kItems][kV], nw[kItems][kV];
-    uint32_t mw[kItems], nm[kItems];
-    auto load = [&](int s, u32x4 (&c)[kItems][kV], uint32_t (&m)[kItems]) {
+    u32x4 cw[kItems][kV];
+    uint32_t mw[kItems];
+    auto load = [&](int s) {
 #pragma unroll
       for (int i = 0; i < kItems; ++i) {
         if (WBF16 && is_w[i]) {
 #pragma unroll
-          for (int v = 0; v < kV; ++v) c[i][v] = vsrc[i][(int64_t)s * 8 + v];
+          for (int v = 0; v < kV; ++v) cw[i][v] = vsrc[i][(int64_t)s * 8 + v];
         } else {
-          c[i][0] = *reinterpret_cast<const u32x4 *>(src[i] + (int64_t)s * 32);
-          m[i] = msrc[i][s];
+          cw[i][0] = *reinterpret_cast<const u32x4 *>(src[i] + (int64_t)s * 32);
+          mw[i] = msrc[i][s];
         }
       }
     };
-    load(0, cw, mw);
+    load(0);
     for (int s = 0; s < nsteps; ++s) {
-      if (s + 1 < nsteps) load(s + 1, nw, nm);
       uint8_t *buf = smem + (s & 1) * S::kBufBytes;
 #pragma unroll
       for (int i = 0; i < kItems; ++i) {
@@ -428,19 +436,14 @@ __global__ __launch_bounds__((HSmem<RES, BN>::kThreads)) void hif4_gemm_kernel(
             *reinterpret_cast<u32x4 *>(buf + hswz(lrow[i], 4 * h + q)) = cw[i][q % kV];
         } else {
           const uint32_t d[4] = {cw[i][0].x, cw[i][0].y, cw[i][0].z, cw[i][0].w};
+          const HalfUnits u = half_units(mw[i], h);
 #pragma unroll
           for (int q = 0; q < 4; ++q)
-            *reinterpret_cast<u32x4 *>(buf + hswz(lrow[i], 4 * h + q)) =
-                decode8_bf16(d[q], mw[i], 4 * h + q);
+            *reinterpret_cast<u32x4 *>(buf + hswz(lrow[i], 4 * h + q)) = decode8_bf16(d[q], u, q);
         }
       }
+      load(min(s + 1, nsteps - 1));
       __syncthreads();
-#pragma unroll
-      for (int i = 0; i < kItems; ++i) {
-#pragma unroll
-        for (int v = 0; v < kV; ++v) cw[i][v] = nw[i][v];
-        mw[i] = nm[i];
-      }
     }
     return;
   }
@@ -730,7 +733,7 @@ __global__ __launch_bounds__(WAVES * 64) void hif4_gemm_few_kernel(
             if (lane + 64 * i < (RES ? 2 : 1) * ms * 16) {
               const XItem it = xitem(i, ms);
               *reinterpret_cast<u32x4 *>(X + few_xoff(it.res ? kFewRows + it.row : it.row, it.w)) =
-                  decode8_bf16(xcur.c[i], xcur.m[i], it.w & 7);
+                  decode8_bf16(xcur.c[i], half_units(xcur.m[i], (it.w >> 2) & 1), it.w & 3);
             }
           }
         } else {
@@ -739,7 +742,7 @@ __global__ __launch_bounds__(WAVES * 64) void hif4_gemm_few_kernel(
             const int t = lane + 64 * i, row = (t >> 4) & 15, w = t & 15;
             const bool res = RES && t >= 256;
             *reinterpret_cast<u32x4 *>(X + few_xoff(res ? kFewRows + row : row, w)) =
-                decode8_bf16(xcur.c[i], xcur.m[i], w & 7);
+                decode8_bf16(xcur.c[i], half_units(xcur.m[i], (w >> 2) & 1), w & 3);
           }
         }
         // Weight pieces in registers, once per chunk for all its slices.
@@ -753,7 +756,7 @@ __global__ __launch_bounds__(WAVES * 64) void hif4_gemm_few_kernel(
               } else {
                 const uint32_t words[4] = {wcur.w[f][0].x, wcur.w[f][0].y, wcur.w[f][0].z,
                                            wcur.w[f][0].w};
-                wp[f][jj] = decode8_bf16(words[jj], wcur.m[f], 4 * (g & 1) + jj);
+                wp[f][jj] = decode8_bf16(words[jj], half_units(wcur.m[f], g & 1), jj);
               }
             }
           }
