@@ -65,6 +65,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "gemm_common.h"
 #include "rfq_internal.h"
@@ -265,6 +266,16 @@ __global__ __launch_bounds__(256) void hif4_dequant_kernel(
   }
 }
 
+// W (rows a multiple of 32) to bf16 in the operand order that
+// hif4_gemm_ordered_kernel reads.  A lane decodes one half (32 elements) of a
+// K block of one row: a wave reads 32 bytes of each of 32 rows and writes 1 KB
+// pieces in runs of 512 bytes; the four waves of a workgroup take consecutive
+// K blocks of the same rows.
+__global__ __launch_bounds__(256) void hif4_order_kernel(const uint8_t *__restrict__ codes,
+                                                         const uint32_t *__restrict__ meta,
+                                                         int64_t items, int64_t K,
+                                                         uint16_t *__restrict__ out);
+
 // ---------------------------------------------------------------- product
 
 constexpr int kBM = 128;                       // tile: activation rows x BN weight rows
@@ -333,6 +344,75 @@ __device__ __forceinline__ u32x4 decode8_bf16(uint32_t w, const HalfUnits &u, in
   };
   return u32x4{pair(a[0] * ua, b[0] * ua), pair(a[1] * ua, b[1] * ua), pair(c[0] * ub, d[0] * ub),
                pair(c[1] * ub, d[1] * ub)};
+}
+
+__global__ __launch_bounds__(256) void hif4_order_kernel(const uint8_t *__restrict__ codes,
+                                                         const uint32_t *__restrict__ meta,
+                                                         int64_t items, int64_t K,
+                                                         uint16_t *__restrict__ out) {
+  const int64_t kblocks = K / kH, stride = (int64_t)gridDim.x * 4;
+  const int lane = threadIdx.x & 63, row = lane & 31, h = lane >> 5;
+  // Item: K block it mod kblocks of the 32 rows from 32 (it / kblocks).
+  for (int64_t it = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); it < items; it += stride) {
+    const int64_t rb = it / kblocks, kb = it % kblocks, r = 32 * rb + row;
+    const u32x4 c = *reinterpret_cast<const u32x4 *>(codes + r * (K / 2) + 32 * kb + 16 * h);
+    const HalfUnits u = half_units(meta[r * kblocks + kb], h);
+    const uint32_t d[4] = {c.x, c.y, c.z, c.w};
+    // Word q: K values 16 (2 h + q / 2) + 8 (q mod 2) of the block.
+    u32x4 *o = reinterpret_cast<u32x4 *>(out + rb * 32 * K + kb * (32 * kH));
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o[64 * (2 * h + q / 2) + 32 * (q & 1) + row] = decode8_bf16(d[q], u, q);
+  }
+}
+
+// A consumer wave's sub-tile of Z, rows from m0 and columns from n0: lane
+// holds Z[m][n .. n+3] for n = 8a + 4 (lane / 32) (a = 0..3) of each fragment
+// (weights are the first MFMA operand).  The lane is formed here rather than
+// kept from before the loop (that value is otherwise held across the loop at
+// the register limit).
+template <bool ZBF16, int FN>
+__device__ __forceinline__ void store_tile(const v16f (&acc)[kFM][FN], int64_t m0, int64_t n0,
+                                           int64_t M, int64_t N, void *z) {
+  const bool vec_ok = (N & 3) == 0;
+  const int elane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  const int64_t erow0 = m0 + (elane & 31);
+  const int64_t ecol0 = n0 + 4 * (elane >> 5);
+#pragma unroll
+  for (int i = 0; i < kFM; ++i) {
+    const int64_t m = erow0 + 32 * i;
+    if (m >= M) continue;
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const int64_t n = ecol0 + 32 * j + 8 * a;
+        const v16f &c = acc[i][j];
+        if constexpr (ZBF16) {
+          uint16_t *zp = reinterpret_cast<uint16_t *>(z) + m * N + n;
+          if (vec_ok && n + 3 < N) {
+            uint2 w;
+            w.x = bf16x2_rne(c[4 * a], c[4 * a + 1]);
+            w.y = bf16x2_rne(c[4 * a + 2], c[4 * a + 3]);
+            *reinterpret_cast<uint2 *>(zp) = w;
+          } else {
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+              if (n + b < N) zp[b] = (uint16_t)bf16_rne(c[4 * a + b]);
+          }
+        } else {
+          float *zp = reinterpret_cast<float *>(z) + m * N + n;
+          if (vec_ok && n + 3 < N) {
+            *reinterpret_cast<float4 *>(zp) =
+                make_float4(c[4 * a], c[4 * a + 1], c[4 * a + 2], c[4 * a + 3]);
+          } else {
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+              if (n + b < N) zp[b] = c[4 * a + b];
+          }
+        }
+      }
+    }
+  }
 }
 
 // WBF16: the weights come as bf16 values wv[N][K] (for example HiF4 weights
@@ -488,51 +568,335 @@ __global__ __launch_bounds__((HSmem<RES, BN>::kThreads)) void hif4_gemm_kernel(
     }
   }
 
-  // ---- epilogue: lane holds Z[m][n .. n+3] for n = 8a + 4 half (a = 0..3)
-  // of each fragment (weights are the first MFMA operand).  The lane's row
-  // and column origins are formed here from the thread index rather than
-  // kept from before the loop (that value is otherwise held across the
-  // loop at the register limit).
-  const bool vec_ok = (N & 3) == 0;
-  const int elane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-  const int64_t erow0 = m0 + wmi * kTM + (elane & 31);
-  const int64_t ecol0 = n0 + wni * kTN + 4 * (elane >> 5);
+  store_tile<ZBF16, kFN>(acc, m0 + wmi * kTM, n0 + wni * kTN, M, N, z);
+}
+
+// ------------------------------------- product on weights in operand order
+//
+// W decoded to bf16 beforehand in the order the MFMAs take it (operand order:
+// per 32 weight rows and 16 K values 1 KB, lane l's 16 bytes at 16 l: row l mod
+// 32, K values 8 (l / 32) .. +7), so that a consumer wave loads its weight
+// fragments from L2 straight into registers, one K block ahead, and only the
+// activations pass through LDS.  The kernel above moves 64 KB into and 128 KB
+// out of LDS per K block and 128 x 256 tile, next to 2048 cycles of MFMAs per
+// SIMD; here it is 32 KB and 64 KB, and half the waves decode.  Each SIMD runs
+// one producer and one consumer wave (256 registers each: 128 accumulators, a
+// K block of weight fragments, two sets of activation fragments).  Three LDS
+// buffers: while the consumers multiply step s they read the first fragments
+// of step s + 1, and the producers write step s + 2; one barrier per step.
+// The MFMAs and their order are the kernel's above, so are the bits.  Measured
+// with the residual, W's decode included: 4096 rows x 12288 x 4096 730 -> 668 us,
+// 4000 x 5120 x 13824 1110 -> 978 us; of the 648 us of the product itself 120
+// are the decode's (567 with the codes written undecoded) and the MFMAs alone
+// take 437 at the 1.8 GHz that the chip holds meanwhile.
+template <bool RES>
+struct OSmem {
+  static constexpr int kRows = (RES ? 2 : 1) * kBM;
+  static constexpr int kBufBytes = kRows * kRowBytes;
+  static constexpr int kBytes = 3 * kBufBytes;
+};
+constexpr int kOProducers = 4, kOThreads = (kOProducers + 4) * 64;
+constexpr int kOBN = 256;
+
+template <bool RES, bool ZBF16>
+__global__ __launch_bounds__(kOThreads, 2) void hif4_gemm_ordered_kernel(
+    const uint8_t *__restrict__ qc, const uint32_t *__restrict__ qm,
+    const uint8_t *__restrict__ rc, const uint32_t *__restrict__ rm,
+    const uint16_t *__restrict__ wv, int64_t M, int64_t N, int64_t K, void *__restrict__ z) {
+  using S = OSmem<RES>;
+  constexpr int kTN = kOBN / 2, kFN = kTN / 32, kKK = kH / 16;
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+  const int ntm = (int)((M + kBM - 1) / kBM), ntn = (int)((N + kOBN - 1) / kOBN);
+  int tm, tn;
+  tile_coords<8>(blockIdx.x, ntm, ntn, tm, tn);
+  const int64_t m0 = (int64_t)tm * kBM, n0 = (int64_t)tn * kOBN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nsteps = (int)(K / kH);
+  const int64_t kbytes = K / 2, kblocks = K / kH;
+
+  if (wave < kOProducers) {
+    // ---- producer: lane takes half (lane mod 2) of rows tid / 2 + 128 i.
+    constexpr int kItems = S::kRows * 2 / (kOProducers * 64);
+    const int h = tid & 1, row = tid / 2;
+    const int64_t grow = min(m0 + row, M - 1);
+    const u32x4 *src[kItems];
+    const uint32_t *msrc[kItems];
 #pragma unroll
-  for (int i = 0; i < kFM; ++i) {
-    const int64_t m = erow0 + 32 * i;
-    if (m >= M) continue;
+    for (int i = 0; i < kItems; ++i) {
+      src[i] = reinterpret_cast<const u32x4 *>((i ? rc : qc) + grow * kbytes + 16 * h);
+      msrc[i] = (i ? rm : qm) + grow * kblocks;
+    }
+    u32x4 c[kItems];
+    uint32_t m[kItems];
+    auto load = [&](int s) {
+#pragma unroll
+      for (int i = 0; i < kItems; ++i) {
+        c[i] = src[i][2 * (int64_t)s];
+        m[i] = msrc[i][s];
+      }
+    };
+    auto produce = [&](int s, int buf) {
+      uint8_t *b = smem + buf * S::kBufBytes;
+#pragma unroll
+      for (int i = 0; i < kItems; ++i) {
+        const uint32_t d[4] = {c[i].x, c[i].y, c[i].z, c[i].w};
+        const HalfUnits u = half_units(m[i], h);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<u32x4 *>(b + hswz(kBM * i + row, 4 * h + q)) = decode8_bf16(d[q], u, q);
+      }
+      load(min(s + 1, nsteps - 1));
+    };
+    load(0);
+    produce(0, 0);
+    if (nsteps > 1) produce(1, 1);
+    __syncthreads();
+    int buf = 2;
+    for (int s = 0; s < nsteps; ++s) {
+      if (s + 2 < nsteps) produce(s + 2, buf);
+      buf = buf == 2 ? 0 : buf + 1;
+      __syncthreads();
+    }
+    return;
+  }
+
+  // ---- consumer: 2 x 2 waves, each 64 activation rows x 128 weight rows.
+  const int cw_ = wave - kOProducers, wmi = cw_ >> 1, wni = cw_ & 1;
+  const int frow = lane & 31, half = lane >> 5;
+  v16f acc[kFM][kFN];
+#pragma unroll
+  for (int i = 0; i < kFM; ++i)
+#pragma unroll
+    for (int j = 0; j < kFN; ++j) acc[i][j] = v16f{};
+
+  // Weight fragments: 32-row block (n0 + wni kTN) / 32 + j (the last one where
+  // that is past N; its columns are not stored), K values 16 kk of a step at
+  // 1024 kk bytes.
+  const __amdgpu_buffer_rsrc_t bw = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t *>(wv), (short)0, (int)(N * K * 2), 0x00020000);
+  uint32_t w_off[kFN];
+#pragma unroll
+  for (int j = 0; j < kFN; ++j)
+    w_off[j] = (uint32_t)(min((n0 + wni * kTN) / 32 + j, N / 32 - 1) * (64 * K) + 16 * lane);
+  u32x4 wf[kKK][kFN];
+  auto load_w = [&](int s, int kk, int j) {
+    wf[kk][j] = __builtin_amdgcn_raw_buffer_load_b128(bw, w_off[j] + 1024 * kk, 4096 * s, 0);
+  };
+  struct XFrag { v8bf q[kFM], r[RES ? kFM : 1]; };
+  auto read_x = [&](int buf, int kk, XFrag &x) {
+    const uint8_t *b = smem + buf * S::kBufBytes;
+#pragma unroll
+    for (int i = 0; i < kFM; ++i) {
+      x.q[i] = *reinterpret_cast<const v8bf *>(b + hswz(wmi * kTM + 32 * i + frow, 2 * kk + half));
+      if constexpr (RES)
+        x.r[i] =
+            *reinterpret_cast<const v8bf *>(b + hswz(kBM + wmi * kTM + 32 * i + frow, 2 * kk + half));
+    }
+  };
+  // 16 K values of a step against the activation fragments in x; the next
+  // ones are read into nx meanwhile and each weight fragment's registers take
+  // the same fragment of step ns after its last MFMA (three quarters of a
+  // step ahead of its use).
+  auto quarter = [&](int kk, const XFrag &x, int nbuf, int nkk, XFrag &nx, int ns) {
+    read_x(nbuf, nkk, nx);
+#pragma unroll
+    for (int j = 0; j < kFN; ++j) {
+      const v8bf w = __builtin_bit_cast(v8bf, wf[kk][j]);
+#pragma unroll
+      for (int i = 0; i < kFM; ++i)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, x.q[i], acc[i][j], 0, 0, 0);
+      if constexpr (RES) {
+#pragma unroll
+        for (int i = 0; i < kFM; ++i)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, x.r[i], acc[i][j], 0, 0, 0);
+      }
+      load_w(ns, kk, j);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x100, RES ? 2 * kFM : kFM, 0);   // LDS reads
+#pragma unroll
+    for (int j = 0; j < kFN; ++j) {
+      __builtin_amdgcn_sched_group_barrier(0x008, RES ? 2 * kFM : kFM, 0);   // MFMAs
+      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                     // global load
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  static_assert(kKK == 4, "two rounds of the two activation fragment sets");
+#pragma unroll
+  for (int kk = 0; kk < kKK; ++kk)
+#pragma unroll
+    for (int j = 0; j < kFN; ++j) load_w(0, kk, j);
+  XFrag xa, xb;
+  __syncthreads();
+  read_x(0, 0, xa);
+  int buf = 0;
+  for (int s = 0; s < nsteps; ++s) {
+    const int nbuf = buf == 2 ? 0 : buf + 1, ns = min(s + 1, nsteps - 1);
+    quarter(0, xa, buf, 1, xb, ns);
+    quarter(1, xb, buf, 2, xa, ns);
+    quarter(2, xa, buf, 3, xb, ns);
+    quarter(3, xb, nbuf, 0, xa, ns);
+    buf = nbuf;
+    __syncthreads();
+  }
+  store_tile<ZBF16, kFN>(acc, m0 + wmi * kTM, n0 + wni * kTN, M, N, z);
+}
+
+// The same on 128 x 512 tiles, for grids that fill their rounds of workgroups
+// with them: 2 x 4 waves of 64 x 128, two per SIMD, each of which also decodes
+// (one code word per lane and 16 K values, between its MFMAs), so that the
+// activations are decoded N / 512 times instead of N / 256.  Weight fragments
+// are loaded two quarters of a step ahead (the two waves of a SIMD take turns,
+// so that is as long as four in the kernel above, whose lead spills here).
+constexpr int kOWideN = 512;
+
+template <bool RES, bool ZBF16>
+__global__ __launch_bounds__(kOThreads, 2) void hif4_gemm_ordered_wide_kernel(
+    const uint8_t *__restrict__ qc, const uint32_t *__restrict__ qm,
+    const uint8_t *__restrict__ rc, const uint32_t *__restrict__ rm,
+    const uint16_t *__restrict__ wv, int64_t M, int64_t N, int64_t K, void *__restrict__ z) {
+  using S = OSmem<RES>;
+  constexpr int kTN = 128, kFN = kTN / 32, kKK = kH / 16;
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+  const int ntm = (int)((M + kBM - 1) / kBM), ntn = (int)((N + kOWideN - 1) / kOWideN);
+  int tm, tn;
+  tile_coords<8>(blockIdx.x, ntm, ntn, tm, tn);
+  const int64_t m0 = (int64_t)tm * kBM, n0 = (int64_t)tn * kOWideN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wmi = wave >> 2, wni = wave & 3;
+  const int frow = lane & 31, half = lane >> 5;
+  const int nsteps = (int)(K / kH);
+  const int64_t kbytes = K / 2, kblocks = K / kH;
+
+  // Decoding: this lane's half row of a K block, LDS row tid / 2 (q rows, then
+  // r rows; without the residual waves 0-3 decode).
+  const bool decodes = RES || wave < 4;
+  const int dh = tid & 1, drow = tid / 2;
+  const int64_t grow = min(m0 + drow % kBM, M - 1);
+  const bool is_r = RES && drow >= kBM;
+  const u32x4 *src = reinterpret_cast<const u32x4 *>((is_r ? rc : qc) + grow * kbytes + 16 * dh);
+  const uint32_t *msrc = (is_r ? rm : qm) + grow * kblocks;
+  struct Codes { u32x4 c; uint32_t m; };
+  auto load_codes = [&](int s, Codes &o) {
+    o.c = src[2 * (int64_t)s];
+    o.m = msrc[s];
+  };
+  auto decode = [&](const Codes &k, int q, int buf) {
+    const uint32_t d[4] = {k.c.x, k.c.y, k.c.z, k.c.w};
+    *reinterpret_cast<u32x4 *>(smem + buf * S::kBufBytes + hswz(drow, 4 * dh + q)) =
+        decode8_bf16(d[q], half_units(k.m, dh), q);
+  };
+
+  // Weight fragments: 32-row block (n0 + wni kTN) / 32 + j (the last one where
+  // that is past N; its columns are not stored), K values 16 kk of step s at
+  // 4096 s + 1024 kk bytes.
+  const __amdgpu_buffer_rsrc_t bw = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t *>(wv), (short)0, (int)(N * K * 2), 0x00020000);
+  uint32_t w_off[kFN];
+#pragma unroll
+  for (int j = 0; j < kFN; ++j)
+    w_off[j] = (uint32_t)(min((n0 + wni * kTN) / 32 + j, N / 32 - 1) * (64 * K) + 16 * lane);
+  constexpr int WR = 2;   // quarters ahead
+  u32x4 wf[WR][kFN];
+  auto load_w = [&](int st, int slot, int j) {   // st: quarter step 4 s + kk
+    wf[slot][j] =
+        __builtin_amdgcn_raw_buffer_load_b128(bw, w_off[j], 1024 * min(st, kKK * nsteps - 1), 0);
+  };
+  struct XFrag { v8bf q[kFM], r[RES ? kFM : 1]; };
+  auto read_x = [&](int buf, int kk, XFrag &x) {
+    const uint8_t *b = smem + buf * S::kBufBytes;
+#pragma unroll
+    for (int i = 0; i < kFM; ++i) {
+      x.q[i] = *reinterpret_cast<const v8bf *>(b + hswz(wmi * kTM + 32 * i + frow, 2 * kk + half));
+      if constexpr (RES)
+        x.r[i] =
+            *reinterpret_cast<const v8bf *>(b + hswz(kBM + wmi * kTM + 32 * i + frow, 2 * kk + half));
+    }
+  };
+  v16f acc[kFM][kFN];
+#pragma unroll
+  for (int i = 0; i < kFM; ++i)
+#pragma unroll
+    for (int j = 0; j < kFN; ++j) acc[i][j] = v16f{};
+
+  // Quarter kk of step s: 16 K values against the activation fragments in x;
+  // the next ones are read into nx meanwhile, each weight fragment's registers
+  // take the fragment WR quarters ahead after its last MFMA, and (DEC) one
+  // of the four code words of step s + 2 is decoded.
+  auto quarter = [&](int s, auto kk_tag, const XFrag &x, int nbuf, XFrag &nx, const Codes &k,
+                     int dbuf, auto dec_tag) {
+    constexpr int kk = decltype(kk_tag)::value;
+    constexpr bool DEC = decltype(dec_tag)::value;
+    constexpr int kNM = RES ? 2 * kFM : kFM;       // MFMAs per weight fragment
+    read_x(nbuf, (kk + 1) % kKK, nx);
+#pragma unroll
+    for (int j = 0; j < kFN; ++j) {
+      const v8bf w = __builtin_bit_cast(v8bf, wf[kk % WR][j]);
+#pragma unroll
+      for (int i = 0; i < kFM; ++i)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, x.q[i], acc[i][j], 0, 0, 0);
+      if constexpr (RES) {
+#pragma unroll
+        for (int i = 0; i < kFM; ++i)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, x.r[i], acc[i][j], 0, 0, 0);
+      }
+      load_w(kKK * s + kk + WR, kk % WR, j);
+    }
+    if constexpr (DEC) decode(k, kk, dbuf);
+    __builtin_amdgcn_sched_group_barrier(0x100, kNM, 0);   // LDS reads
 #pragma unroll
     for (int j = 0; j < kFN; ++j) {
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const int64_t n = ecol0 + 32 * j + 8 * a;
-        const v16f &c = acc[i][j];
-        if constexpr (ZBF16) {
-          uint16_t *zp = reinterpret_cast<uint16_t *>(z) + m * N + n;
-          if (vec_ok && n + 3 < N) {
-            uint2 w;
-            w.x = bf16x2_rne(c[4 * a], c[4 * a + 1]);
-            w.y = bf16x2_rne(c[4 * a + 2], c[4 * a + 3]);
-            *reinterpret_cast<uint2 *>(zp) = w;
-          } else {
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-              if (n + b < N) zp[b] = (uint16_t)bf16_rne(c[4 * a + b]);
-          }
-        } else {
-          float *zp = reinterpret_cast<float *>(z) + m * N + n;
-          if (vec_ok && n + 3 < N) {
-            *reinterpret_cast<float4 *>(zp) =
-                make_float4(c[4 * a], c[4 * a + 1], c[4 * a + 2], c[4 * a + 3]);
-          } else {
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-              if (n + b < N) zp[b] = c[4 * a + b];
-          }
-        }
+      for (int i = 0; i < kNM; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                    // MFMA
+        if constexpr (DEC) __builtin_amdgcn_sched_group_barrier(0x002, RES ? 2 : 4, 0);   // VALU
       }
+      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                      // global load
     }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  using T = std::true_type;
+  using F = std::false_type;
+
+  // Three LDS buffers: while step s is multiplied the waves read the first
+  // fragments of step s + 1 and write step s + 2; one barrier per step.
+  Codes kc, kn;
+  load_codes(0, kc);
+  load_codes(min(1, nsteps - 1), kn);
+#pragma unroll
+  for (int kk = 0; kk < WR; ++kk)
+#pragma unroll
+    for (int j = 0; j < kFN; ++j) load_w(kk, kk, j);
+  if (decodes) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) decode(kc, q, 0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) decode(kn, q, 1);
   }
+  load_codes(min(2, nsteps - 1), kc);
+  XFrag xa, xb;
+  __syncthreads();
+  read_x(0, 0, xa);
+  int buf = 0;
+  auto step = [&](int s, auto dec_tag) {
+    const int nbuf = buf == 2 ? 0 : buf + 1, dbuf = nbuf == 2 ? 0 : nbuf + 1;
+    load_codes(min(s + 3, nsteps - 1), kn);
+    __builtin_amdgcn_sched_barrier(0);
+    quarter(s, std::integral_constant<int, 0>{}, xa, buf, xb, kc, dbuf, dec_tag);
+    quarter(s, std::integral_constant<int, 1>{}, xb, buf, xa, kc, dbuf, dec_tag);
+    quarter(s, std::integral_constant<int, 2>{}, xa, buf, xb, kc, dbuf, dec_tag);
+    quarter(s, std::integral_constant<int, 3>{}, xb, nbuf, xa, kc, dbuf, dec_tag);
+    kc = kn;
+    buf = nbuf;
+    __syncthreads();
+  };
+  // The last two steps write buffers that nothing reads (of the last K block).
+  if (decodes)
+    for (int s = 0; s < nsteps; ++s) step(s, T{});
+  else
+    for (int s = 0; s < nsteps; ++s) step(s, F{});
+  store_tile<ZBF16, kFN>(acc, m0 + wmi * kTM, n0 + wni * kTN, M, N, z);
 }
 
 // ---------------------------------------------------------------- few rows
@@ -969,6 +1333,48 @@ hipError_t launch_hg(const uint8_t *qc, const uint32_t *qm, const uint8_t *rc,
 }
 
 
+int64_t ordered_tiles(int64_t M, int64_t N, int64_t bn) {
+  return ((M + kBM - 1) / kBM) * ((N + bn - 1) / bn);
+}
+
+// 512-wide tiles where their rounds of 256 workgroups take less time; one
+// takes 1.86 times a round of 256-wide ones (4096 rows x 12288 x 4096, 3 against
+// 6 rounds, W's decode included: 629 against 674 us; 1024 rows, 1 against 2:
+// 195 against 219; 2048 x 4096 x 12288, 1 and 1: 463 against 347; 4000 x 5120 x
+// 13824, 2 and 3: 1150 against 989).
+bool ordered_wide(int64_t M, int64_t N) {
+  auto rounds = [&](int64_t bn) {
+    return (ordered_tiles(M, N, bn) + kFillTiles - 1) / kFillTiles;
+  };
+  return 186 * rounds(kOWideN) < 100 * rounds(kOBN);
+}
+
+// Decodes W into wv (N a multiple of 32, N K values) and multiplies.
+hipError_t launch_ordered(const uint8_t *qc, const uint32_t *qm, const uint8_t *rc,
+                          const uint32_t *rm, const uint8_t *wc, const uint32_t *wm, uint16_t *wv,
+                          int64_t M, int64_t N, int64_t K, void *z, bool z_bf16,
+                          hipStream_t stream) {
+  const int64_t items = N / 32 * (K / kH);
+  hif4_order_kernel<<<dim3((unsigned)std::min<int64_t>((items + 3) / 4, kLoopGrid)), 256, 0,
+                      stream>>>(wc, wm, items, K, wv);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  auto go = [&](auto res_tag, auto bf_tag) {
+    constexpr bool RES = decltype(res_tag)::value, ZB = decltype(bf_tag)::value;
+    const bool wide = ordered_wide(M, N);
+    auto kern = wide ? hif4_gemm_ordered_wide_kernel<RES, ZB> : hif4_gemm_ordered_kernel<RES, ZB>;
+    static std::atomic<bool> done[2][kMaxDevices];
+    e = set_lds_limit(done[wide], reinterpret_cast<const void *>(kern), OSmem<RES>::kBytes);
+    if (e != hipSuccess) return e;
+    const int64_t tiles = ordered_tiles(M, N, wide ? kOWideN : kOBN);
+    kern<<<dim3((unsigned)tiles), dim3(kOThreads), OSmem<RES>::kBytes, stream>>>(qc, qm, rc, rm, wv,
+                                                                                 M, N, K, z);
+    return hipGetLastError();
+  };
+  if (rc) return z_bf16 ? go(std::true_type{}, std::true_type{}) : go(std::true_type{}, std::false_type{});
+  return z_bf16 ? go(std::false_type{}, std::true_type{}) : go(std::false_type{}, std::false_type{});
+}
+
 template <int STEPS>
 hipError_t launch_hq(const void *x, bool bf16_in, int64_t nunits, uint8_t *qc, uint32_t *qm,
                      uint8_t *rc, uint32_t *rm, hipStream_t stream) {
@@ -1104,6 +1510,9 @@ hipError_t launch_hif4_gemm_split(const uint8_t *q_codes, const uint32_t *q_meta
   const SplitPlan p = hif4_split_plan(M, N, K);
   if (p.decode_w && work != nullptr && work_bytes >= p.work_bytes) {
     uint16_t *wv = reinterpret_cast<uint16_t *>(work);
+    if (N % 32 == 0)
+      return launch_ordered(q_codes, q_meta, r_codes, r_meta, w_codes, w_meta, wv, M, N, K, z,
+                            z_bf16, stream);
     const hipError_t e = launch_hif4_dequant(w_codes, w_meta, N * K, wv, true, stream);
     if (e != hipSuccess) return e;
     return launch_hif4_gemm(q_codes, q_meta, r_codes, r_meta, nullptr, nullptr, wv, M, N, K, z,
