@@ -1,16 +1,21 @@
-"""Builds librfq.so (the HIP kernels and the C ABI) in-tree for gfx950."""
+"""Builds librfq.so (the HIP kernels and the C ABI) in-tree for gfx950, and
+_rfq_calls.so (the binding's native calls; host code only)."""
 import glob
 import os
 import subprocess
+import sysconfig
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 REPO_DIR = os.path.dirname(PKG_DIR)
 LIB_PATH = os.path.join(PKG_DIR, "librfq.so")
+CALLS_PATH = os.path.join(PKG_DIR, "_rfq_calls.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # -packed-fp32-ops: no packed fp32 VALU instructions are generated.
 FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
 ]
@@ -20,24 +25,54 @@ def sources():
     return sorted(glob.glob(os.path.join(PKG_DIR, "csrc", "*.hip")))
 
 
-def build(verbose=False, extra_flags=(), out=LIB_PATH):
-    """Compile every source under csrc/ into librfq.so, or into `out` with
-    extra compiler flags (always recompiles)."""
-    tmp = out + ".tmp"
-    cmd = [HIPCC, *FLAGS, *extra_flags,
-           "-I", os.path.join(REPO_DIR, "include"),
-           "-I", os.path.join(PKG_DIR, "csrc"),
-           *sources(), "-o", tmp]
+def build_calls(verbose=False):
+    """Compile csrc_host/ against the installed torch into _rfq_calls.so."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    inc = os.path.join(root, "include")
+    tmp = CALLS_PATH + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+           "-isystem", "/opt/rocm/include", "-I", sysconfig.get_paths()["include"],
+           os.path.join(PKG_DIR, "csrc_host", "calls.cpp"), "-o", tmp,
+           "-L", os.path.join(root, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
-    err = "\n".join(l for l in res.stderr.splitlines()
-                    if "packed-fp32-ops" not in l)
     if res.returncode != 0:
-        raise RuntimeError("librfq build failed:\n" + err)
-    if verbose and err.strip():
-        print(err)
+        raise RuntimeError("_rfq_calls build failed:\n" + res.stderr)
+    os.replace(tmp, CALLS_PATH)
+    return CALLS_PATH
+
+
+def build(verbose=False, extra_flags=(), out=LIB_PATH):
+    """Compile every source under csrc/ into librfq.so and the native calls, or
+    only the library into `out` with extra compiler flags (always recompiles)."""
+    tmp = out + ".tmp"
+    flags = [*FLAGS, *extra_flags]
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        err = "\n".join(l for l in res.stderr.splitlines() if "packed-fp32-ops" not in l)
+        if res.returncode != 0:
+            raise RuntimeError("librfq build failed:\n" + err)
+        if verbose and err.strip():
+            print(err)
+
+    with tempfile.TemporaryDirectory() as objs, ThreadPoolExecutor(8) as pool:
+        def compile_one(src):
+            obj = os.path.join(objs, os.path.basename(src) + ".o")
+            run([HIPCC, *flags, "-I", os.path.join(REPO_DIR, "include"),
+                 "-I", os.path.join(PKG_DIR, "csrc"), "-c", src, "-o", obj])
+            return obj
+        run([HIPCC, *flags, "-shared", *pool.map(compile_one, sources()), "-o", tmp])
     os.replace(tmp, out)
+    if out == LIB_PATH:
+        build_calls(verbose)
     return out
 
 

@@ -10,12 +10,14 @@ contiguous device tensors on the current device; outputs are allocated when
 not passed in.
 """
 import ctypes
+import importlib.util
 import os
 
 import torch
 
 _PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG_DIR, "librfq.so")
+CALLS_PATH = os.path.join(_PKG_DIR, "_rfq_calls.so")
 
 RFQ_F32 = 0
 RFQ_BF16 = 1
@@ -47,6 +49,9 @@ RFQ_PHI_RESIDUAL_NONZERO = 0
 RFQ_PHI_SCALE_AT_LEAST = 1
 
 _lib = None
+# The native calls (csrc_host/calls.cpp): the functions below hand them their
+# arguments first and go on in Python where they return None.
+_calls = None
 
 
 class RfqError(RuntimeError):
@@ -97,12 +102,41 @@ def load():
               "rfq_gemm_split", "rfq_hif4_gemm_split",
               "rfq_gemm_split_noalloc"):
         getattr(lib, f).restype = I32
+    _bind_calls(lib)
     lib.rfq_status_str.argtypes = [I32]
     lib.rfq_status_str.restype = ctypes.c_char_p
     lib.rfq_abi_version.argtypes = []
     lib.rfq_abi_version.restype = I32
     _lib = lib
     return lib
+
+
+def _bind_calls(lib):
+    """Loads the native calls once and points them at lib's entry points."""
+    global _calls
+    if _calls is None:
+        if not os.path.exists(CALLS_PATH):
+            raise RuntimeError("_rfq_calls.so is not built (expected at %s); run "
+                               "__graft_entry__.build()" % CALLS_PATH)
+        spec = importlib.util.spec_from_file_location("_rfq_calls", CALLS_PATH)
+        _calls = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(_calls)
+    _calls.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+        lib.rfq_quantize_act, lib.rfq_gemm, lib.rfq_gemm_split, lib.rfq_gemm_workspace_bytes,
+        lib.rfq_gemm_stream, lib.rfq_hif4_quantize, lib.rfq_hif4_gemm, lib.rfq_hif4_gemm_split,
+        lib.rfq_hif4_gemm_workspace_bytes, lib.rfq_gemm_phi, lib.rfq_fallback_map,
+        lib.rfq_gemm_swiglu_quantize)))
+
+
+# dtype codes of out_dtype for the native calls (others: checked in Python).
+_OUT_CODE = {torch.float32: RFQ_F32, torch.bfloat16: RFQ_BF16}
+
+
+def _native(func, *args):
+    """The result of a native call, or None where the Python path takes over."""
+    if _calls is None:
+        load()
+    return getattr(_calls, func)(*args)
 
 
 def rfq_status_str(status):
@@ -239,6 +273,10 @@ def _z_out(out, out_dtype, M, N, device, dev=None):
 def rfq_quantize_act(x, residual=True, out=None, stream=None):
     """X[M][K] -> (q_codes, q_scales, r_codes, r_scales); r_* are None when
     residual is False.  out may supply the four (or two) output tensors."""
+    if out is None and stream is None:
+        r = _native("quantize_act", x, residual)
+        if r is not None:
+            return r
     _need(x, "x", _FLOAT)
     dev = x.get_device()
     if x.dim() != 2:
@@ -278,6 +316,11 @@ def rfq_gemm(q_codes, q_scales, r_codes, r_scales, w_codes, w_scales,
     """Z[M][N] = (deq q + deq r) deq(w)^T; r_* None gives plain MXFP4.
     split=True: rfq_gemm_split with a workspace from torch's allocator where
     the shape splits K (a different fp32 summation order)."""
+    if stream is None:
+        r = _native("gemm", q_codes, q_scales, r_codes, r_scales, w_codes, w_scales,
+                    _OUT_CODE.get(out_dtype, 2), out, split)
+        if r is not None:
+            return r
     M, K = _shape_of_codes(q_codes, "q codes")
     N, Kw = _shape_of_codes(w_codes, "w codes")
     if Kw != K:
@@ -357,6 +400,11 @@ def rfq_gemm_stream(x, w_codes, w_scales, residual=True, out_dtype=torch.float32
                     stream=None):
     """Streaming form: Z[M][N] from X[M][K] (bf16 or fp32) quantized inside the
     product's K loop (primary and, with residual, the quantized residual)."""
+    if stream is None:
+        r = _native("gemm_stream", x, w_codes, w_scales, residual,
+                    _OUT_CODE.get(out_dtype, 2), out)
+        if r is not None:
+            return r
     _need(x, "x", _FLOAT)
     dev = x.get_device()
     if x.dim() != 2:
@@ -378,6 +426,11 @@ def rfq_gemm_phi(q_codes, q_scales, r_codes, r_scales, w_codes, w_scales, phi,
                  out_dtype=torch.float32, out=None, stream=None):
     """RFQ product with a fallback-indicator map phi[ceil(M/64)][ceil(K/256)]
     (uint8; None: phi = 1)."""
+    if stream is None:
+        z = _native("gemm_phi", q_codes, q_scales, r_codes, r_scales, w_codes, w_scales, phi,
+                    _OUT_CODE.get(out_dtype, 2), out)
+        if z is not None:
+            return z
     M, K = _shape_of_codes(q_codes, "q codes")
     N, Kw = _shape_of_codes(w_codes, "w codes")
     if Kw != K:
@@ -399,6 +452,10 @@ def rfq_fallback_map(r_codes, q_scales, rule, threshold=0, out=None, stream=None
     """phi[ceil(M/64)][ceil(K/256)] by RFQ_PHI_RESIDUAL_NONZERO (reads r_codes)
     or RFQ_PHI_SCALE_AT_LEAST (reads q_scales; phi = 1 where a scale byte >=
     threshold)."""
+    if out is None and stream is None:
+        phi = _native("fallback_map", r_codes, q_scales, rule, threshold)
+        if phi is not None:
+            return phi
     if not isinstance(q_scales, torch.Tensor) or q_scales.dim() != 2:
         raise ValueError("q_scales must be a 2-D tensor [M][K/32] (it gives M and K)")
     M, K = q_scales.shape[0], q_scales.shape[1] * 32
@@ -480,6 +537,11 @@ def rfq_gemm_swiglu_quantize(q_codes, q_scales, r_codes, r_scales, wgu_codes, wg
     wgu_* are the quantized interleaved gate/up weights [2 Nh][K]
     (interleave_gate_up).  Returns (hq_codes, hq_scales, hr_codes, hr_scales,
     h or None); hr_* are None when residual is False."""
+    if out is None and stream is None and not return_h:
+        r = _native("gemm_swiglu_quantize", q_codes, q_scales, r_codes, r_scales, wgu_codes,
+                    wgu_scales, residual)
+        if r is not None:
+            return r
     M, K = _shape_of_codes(q_codes, "q codes")
     N2, Kw = _shape_of_codes(wgu_codes, "gate/up codes")
     if Kw != K:
@@ -523,6 +585,10 @@ def _hif4_out(rows, K, device):
 def rfq_hif4_quantize(x, residual=True, out=None, stream=None):
     """X[rows][K] (K a multiple of 64) -> (q_codes, q_meta, r_codes, r_meta)
     in HiF4; r_* are None when residual is False (the weight quantizer)."""
+    if out is None and stream is None:
+        r = _native("hif4_quantize", x, residual)
+        if r is not None:
+            return r
     _need(x, "x", _FLOAT)
     dev = x.get_device()
     if x.dim() != 2:
@@ -586,6 +652,11 @@ def rfq_hif4_gemm(q_codes, q_meta, r_codes, r_meta, w_codes, w_meta,
     split=True: rfq_hif4_gemm_split with a workspace from torch's allocator
     where the shape splits K (a different fp32 summation order) or decodes
     the weights into it (the same bits)."""
+    if stream is None:
+        r = _native("hif4_gemm", q_codes, q_meta, r_codes, r_meta, w_codes, w_meta,
+                    _OUT_CODE.get(out_dtype, 2), out, split)
+        if r is not None:
+            return r
     M, N, K, dev = _hif4_operands(q_codes, q_meta, r_codes, r_meta, w_codes, w_meta)
     z = _z_out(out, out_dtype, M, N, q_codes.device, dev)
     if split:
