@@ -285,12 +285,17 @@ constexpr int kFM = kTM / 32;
 
 // BN = 256 weight rows per tile, or 128 where 256-row tiles would leave CUs
 // idle (fewer activation rows).
-template <bool RES, int BN>
+template <bool RES, int BN, bool WBF16>
 struct HSmem {
   static constexpr int kWRow0 = (RES ? 2 : 1) * kBM;    // q rows, r rows, then w rows
   static constexpr int kRows = kWRow0 + BN;
   static constexpr int kBufBytes = kRows * kRowBytes;
-  static constexpr int kBytes = 2 * kBufBytes;
+  // Three buffers with BN = 128 where W is decoded here (consumers read a
+  // step's first fragments before the barrier that ends the step before it;
+  // bf16 weights gain nothing from it, and two buffers of BN = 256 fill the
+  // LDS).
+  static constexpr int kBufs = BN == 128 && !WBF16 ? 3 : 2;
+  static constexpr int kBytes = kBufs * kBufBytes;
   // Producer waves: each lane decodes two half-block rows per step (8 waves,
   // two per SIMD, with the residual and BN = 256), with BN = 128 one (12 waves,
   // three per SIMD, where 6 left two SIMDs with twice the decode of the others:
@@ -422,14 +427,14 @@ __device__ __forceinline__ void store_tile(const v16f (&acc)[kFM][FN], int64_t m
 // multiplying K columns [s ksplit, (s + 1) ksplit) (ksplit a multiple of 64)
 // and writing its fp32 partial product to z + s M N.
 template <bool RES, bool ZBF16, bool WBF16, int BN, bool SPLIT = false>
-__global__ __launch_bounds__((HSmem<RES, BN>::kThreads)) void hif4_gemm_kernel(
+__global__ __launch_bounds__((HSmem<RES, BN, WBF16>::kThreads)) void hif4_gemm_kernel(
     const uint8_t *__restrict__ qc, const uint32_t *__restrict__ qm,
     const uint8_t *__restrict__ rc, const uint32_t *__restrict__ rm,
     const uint8_t *__restrict__ wc, const uint32_t *__restrict__ wm,
     const uint16_t *__restrict__ wv, int64_t M, int64_t N, int64_t K, void *__restrict__ z,
     int64_t ksplit) {
   static_assert(!SPLIT || !ZBF16, "split partials are fp32");
-  using S = HSmem<RES, BN>;
+  using S = HSmem<RES, BN, WBF16>;
   constexpr int kTN = S::kTN, kFN = S::kFN;
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
 
@@ -505,9 +510,8 @@ __global__ __launch_bounds__((HSmem<RES, BN>::kThreads)) void hif4_gemm_kernel(
         }
       }
     };
-    load(0);
-    for (int s = 0; s < nsteps; ++s) {
-      uint8_t *buf = smem + (s & 1) * S::kBufBytes;
+    auto produce = [&](int s, int b) {
+      uint8_t *buf = smem + b * S::kBufBytes;
 #pragma unroll
       for (int i = 0; i < kItems; ++i) {
         if (WBF16 && is_w[i]) {
@@ -523,7 +527,23 @@ __global__ __launch_bounds__((HSmem<RES, BN>::kThreads)) void hif4_gemm_kernel(
         }
       }
       load(min(s + 1, nsteps - 1));
+    };
+    load(0);
+    if constexpr (S::kBufs == 2) {
+      for (int s = 0; s < nsteps; ++s) {
+        produce(s, s & 1);
+        __syncthreads();
+      }
+    } else {
+      produce(0, 0);
+      if (nsteps > 1) produce(1, 1);
       __syncthreads();
+      int b = 2;
+      for (int s = 0; s < nsteps; ++s) {
+        if (s + 2 < nsteps) produce(s + 2, b);
+        b = b == 2 ? 0 : b + 1;
+        __syncthreads();
+      }
     }
     return;
   }
@@ -540,34 +560,85 @@ __global__ __launch_bounds__((HSmem<RES, BN>::kThreads)) void hif4_gemm_kernel(
   auto frag = [&](const uint8_t *buf, int row, int kk) {
     return *reinterpret_cast<const v8bf *>(buf + hswz(row, 2 * kk + half));
   };
-  for (int s = 0; s < nsteps; ++s) {
-    __syncthreads();
-    const uint8_t *buf = smem + (s & 1) * S::kBufBytes;
+  if constexpr (S::kBufs == 2) {
+    for (int s = 0; s < nsteps; ++s) {
+      __syncthreads();
+      const uint8_t *buf = smem + (s & 1) * S::kBufBytes;
 #pragma unroll
-    for (int kk = 0; kk < kH / 16; ++kk) {
-      v8bf wf[kFN], xf[kFM], rf[RES ? kFM : 1];
+      for (int kk = 0; kk < kH / 16; ++kk) {
+        v8bf wf[kFN], xf[kFM], rf[RES ? kFM : 1];
 #pragma unroll
-      for (int j = 0; j < kFN; ++j) wf[j] = frag(buf, S::kWRow0 + wni * kTN + 32 * j + frow, kk);
+        for (int j = 0; j < kFN; ++j) wf[j] = frag(buf, S::kWRow0 + wni * kTN + 32 * j + frow, kk);
+#pragma unroll
+        for (int i = 0; i < kFM; ++i) {
+          xf[i] = frag(buf, wmi * kTM + 32 * i + frow, kk);
+          if constexpr (RES) rf[i] = frag(buf, kBM + wmi * kTM + 32 * i + frow, kk);
+        }
+#pragma unroll
+        for (int i = 0; i < kFM; ++i)
+#pragma unroll
+          for (int j = 0; j < kFN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[j], xf[i], acc[i][j], 0, 0, 0);
+        if constexpr (RES) {
+#pragma unroll
+          for (int i = 0; i < kFM; ++i)
+#pragma unroll
+            for (int j = 0; j < kFN; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[j], rf[i], acc[i][j], 0, 0, 0);
+        }
+      }
+    }
+
+  } else {
+    // The fragments of the next 16 K values are read before the MFMAs of the
+    // current ones (each was read and waited for before its MFMAs: 300 rows x
+    // 5120 x 13824 252 -> 224 us, split 136 -> 130; 512 x 12288 x 4096 160 ->
+    // 149; a second set of fragments does not fit the registers of BN = 256).
+    struct Frags { v8bf w[kFN], q[kFM], r[RES ? kFM : 1]; };
+    auto read = [&](int b, int kk, Frags &f) {
+      const uint8_t *buf = smem + b * S::kBufBytes;
+#pragma unroll
+      for (int j = 0; j < kFN; ++j) f.w[j] = frag(buf, S::kWRow0 + wni * kTN + 32 * j + frow, kk);
 #pragma unroll
       for (int i = 0; i < kFM; ++i) {
-        xf[i] = frag(buf, wmi * kTM + 32 * i + frow, kk);
-        if constexpr (RES) rf[i] = frag(buf, kBM + wmi * kTM + 32 * i + frow, kk);
+        f.q[i] = frag(buf, wmi * kTM + 32 * i + frow, kk);
+        if constexpr (RES) f.r[i] = frag(buf, kBM + wmi * kTM + 32 * i + frow, kk);
       }
+    };
+    auto multiply = [&](const Frags &f) {
 #pragma unroll
       for (int i = 0; i < kFM; ++i)
 #pragma unroll
         for (int j = 0; j < kFN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[j], xf[i], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.w[j], f.q[i], acc[i][j], 0, 0, 0);
       if constexpr (RES) {
 #pragma unroll
         for (int i = 0; i < kFM; ++i)
 #pragma unroll
           for (int j = 0; j < kFN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[j], rf[i], acc[i][j], 0, 0, 0);
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.w[j], f.r[i], acc[i][j], 0, 0, 0);
       }
+    };
+    auto quarter = [&](const Frags &f, int b, int kk, Frags &next) {
+      read(b, kk, next);
+      multiply(f);
+      __builtin_amdgcn_sched_group_barrier(0x100, kFN + (RES ? 2 : 1) * kFM, 0);   // LDS reads
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    Frags fa, fb;
+    __syncthreads();
+    read(0, 0, fa);
+    int b = 0;
+    for (int s = 0; s < nsteps; ++s) {
+      const int nb = b == 2 ? 0 : b + 1;
+      quarter(fa, b, 1, fb);
+      quarter(fb, b, 2, fa);
+      quarter(fa, b, 3, fb);
+      quarter(fb, nb, 0, fa);
+      b = nb;
+      __syncthreads();
     }
   }
-
   store_tile<ZBF16, kFN>(acc, m0 + wmi * kTM, n0 + wni * kTN, M, N, z);
 }
 
@@ -1196,7 +1267,7 @@ hipError_t launch_tiles(const uint8_t *qc, const uint32_t *qm, const uint8_t *rc
                         const uint32_t *rm, const uint8_t *wc, const uint32_t *wm,
                         const uint16_t *wv, int64_t M, int64_t N, int64_t K, void *z,
                         hipStream_t stream, int parts = 1, int64_t ksplit = 0) {
-  using S = HSmem<RES, BN>;
+  using S = HSmem<RES, BN, WBF16>;
   auto kern = hif4_gemm_kernel<RES, ZBF16, WBF16, BN, SPLIT>;
   static std::atomic<bool> attr_done[kMaxDevices];
   const hipError_t e = set_lds_limit(attr_done, reinterpret_cast<const void *>(kern), S::kBytes);
