@@ -90,6 +90,9 @@ using Mid = Tile<2, 2, 2, 1>;
 // their use), at most two workgroups per CU: for grids of at most one
 // workgroup per CU, where nothing else covers the loads' latency.
 using MidDeep = Tile<2, 2, 2, 2>;
+// 256 x 128, 8 waves of 64 x 64, one workgroup per CU: for grids of one to two
+// 128 x 128 tiles per CU, where half of the CUs would run two and half one.
+using Tall = Tile<4, 2, 2, 2>;
 
 constexpr int kStageK = 128;
 constexpr int kRowBytes = kStageK / 2;
@@ -791,7 +794,9 @@ hipError_t launch(const uint8_t *qc, const uint8_t *qs, const uint8_t *rc,
       return launch<C, RES, ZBF16, SWIGLU, HRES, PHI, true>(qc, qs, rc, rs, wc, ws, M, N, K, z,
                                                             stream, so, phi);
   using L = Layout<C, RES>;
-  static_assert((C::kThreads / 64) * Epi<ZBF16>::kWaveBytes <= L::kBytes, "epilogue staging fits");
+  // The stage buffers or, where that is more, the waves' epilogue staging.
+  constexpr int kEpiBytes = (C::kThreads / 64) * Epi<ZBF16>::kWaveBytes;
+  constexpr int kBaseBytes = L::kBytes > kEpiBytes ? L::kBytes : kEpiBytes;
   void (*kern)(const uint8_t *, const uint8_t *, const uint8_t *, const uint8_t *,
                const uint8_t *, const uint8_t *, int64_t, int64_t, int64_t, void *, SwigluOut,
                const uint8_t *, int64_t);
@@ -800,14 +805,14 @@ hipError_t launch(const uint8_t *qc, const uint8_t *qs, const uint8_t *rc,
   else
     kern = rfq_gemm_mid_kernel<C, RES, ZBF16, SWIGLU, HRES, PHI, GK>;
   // LDS: the two stage buffers, then (PHI) the rows of the indicator map.
-  constexpr int kMaxBytes = L::kBytes + (PHI ? kPhiMapMaxBytes : 0);
+  constexpr int kMaxBytes = kBaseBytes + (PHI ? kPhiMapMaxBytes : 0);
   const int phi_bytes =
       PHI ? (int)(((C::kWaveRows * ((K + kPhiK - 1) / kPhiK)) + 15) / 16 * 16) : 0;
   static std::atomic<bool> attr_done[kMaxDevices];
   const hipError_t e = set_lds_limit(attr_done, reinterpret_cast<const void *>(kern), kMaxBytes);
   if (e != hipSuccess) return e;
   const int64_t ntiles = ((M + C::kBM - 1) / C::kBM) * ((N + C::kBN - 1) / C::kBN);
-  kern<<<dim3((unsigned)ntiles), dim3(C::kThreads), L::kBytes + phi_bytes, stream>>>(
+  kern<<<dim3((unsigned)ntiles), dim3(C::kThreads), kBaseBytes + phi_bytes, stream>>>(
       qc, qs, rc, rs, wc, ws, M, N, K, z, so, phi, K);
   return hipGetLastError();
 }
@@ -864,6 +869,18 @@ int splitk_default_parts(int64_t M, int64_t N, int64_t K) {
 // 1.06-1.23 at 512-576.
 bool use_mid_tiles(int64_t M, int64_t N) {
   return mid_tiles(M, N) < 2 * 256;
+}
+
+// Tall tiles where 128 x 128 ones number between one and two per CU and tall
+// ones at most one.  Same bits.  Measured, 128 x 128 (Mid) against tall: 200
+// rows x 24576 x 4096 (384 against 192 tiles) 35.6 -> 33.2 us, with the SwiGLU
+// epilogue 38.9 -> 35.9, 512 rows x 12288 x 4096 37.2 -> 34.9 (plain 24.5 ->
+// 21.7), 700 x 8192 x 4096 36.4 -> 34.2, 1000 x 5000 x 2912 (320 and 160) 29.8
+// -> 29.6.  One stage in registers: 37.6 with the epilogue, the same without.
+bool use_tall_tiles(int64_t M, int64_t N) {
+  const int64_t mid = mid_tiles(M, N);
+  const int64_t tall = ((M + Tall::kBM - 1) / Tall::kBM) * ((N + Tall::kBN - 1) / Tall::kBN);
+  return mid > 256 && mid < 2 * 256 && tall <= 256;
 }
 
 // MidDeep for `workgroups` 128 x 128 tiles (times parts of K): at most one
@@ -960,6 +977,7 @@ static int64_t big_tile_rows(int64_t M, int64_t N) {
 // rows -> tile shape, for the product with or without a map.
 template <class Go>
 static hipError_t on_tiles(int64_t M, int64_t N, Go go) {
+  if (use_tall_tiles(M, N)) return go(Tall{}, 0, M);
   if (use_mid_tiles(M, N))
     return use_deep_tiles(mid_tiles(M, N)) ? go(MidDeep{}, 0, M) : go(Mid{}, 0, M);
   const int64_t big_rows = std::min<int64_t>(big_tile_rows(M, N) * Big::kBM, M);
@@ -1039,6 +1057,7 @@ hipError_t launch_gemm_swiglu(const uint8_t *q_codes, const uint8_t *q_scales,
                                                wgu_scales, M, N, K, nullptr, stream, so);
   };
   if (!use_mid_tiles(M, N)) return go(Big{});
+  if (use_tall_tiles(M, N)) return go(Tall{});
   return use_deep_tiles(mid_tiles(M, N)) ? go(MidDeep{}) : go(Mid{});
 }
 

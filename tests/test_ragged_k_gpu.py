@@ -29,6 +29,9 @@ SHAPES = [
     (300, 130, 896),         # 28 blocks: 7 whole stages
     (385, 260, 1120),        # 35 blocks: 9 stages
     (2900, 2900, 608),       # 256-wide tiles: 19 blocks, 5 stages
+    (520, 7200, 544),        # 256 x 128 tiles: 17 blocks, 5 stages, ragged rows
+    (700, 5600, 96),         # the same, one short stage
+    (300, 12300, 256),       # the same, two stages, ragged columns
     (2830, 3000, 1440),      # 45 blocks, 12 stages
     (150, 200, 2848),        # split (see below): 89 blocks
 ]
@@ -112,7 +115,7 @@ def test_unaligned_scale_tensors(orc, M, N, K):
 
 @pytest.mark.parametrize("M,N,K", [(1, 70, 512), (16, 300, 1312), (20, 8200, 800), (40, 130, 2048),
                                    (100, 260, 992), (7, 12300, 1024), (100, 12300, 1056),
-                                   (200, 130, 2336), (700, 2900, 1120), (2900, 2900, 608)])
+                                   (200, 130, 2336), (700, 2900, 1120), (520, 7200, 544), (2900, 2900, 608)])
 def test_random_maps(orc, M, N, K):
     """Maps on the few-row, 128-wide and 256-wide kernels (the last two rows of
     256-wide tiles run 128-wide ones): random, one all-ones column and row."""
