@@ -12,8 +12,8 @@
 // load instructions themselves: pointing them at always-cached data does not
 // change the time.)  Where the 256 x 256 tiles would leave CUs idle, the same
 // code runs 128 x 128 tiles (4 waves of 64 x 64, up to three workgroups per
-// CU); each output is accumulated in the same order in both shapes, so they
-// give the same bits.
+// CU) or 256 x 128 ones; each output is accumulated in the same order in all
+// shapes, so they give the same bits.
 //
 // Instruction: v_mfma_scale_f32_32x32x64_f8f6f4 with E2M1 operands: lane l
 // of an operand holds row (l mod 32) and 32 consecutive K values (one MX
@@ -35,7 +35,8 @@
 // fragments of stage st are read from buffer st mod 2 and multiplied while
 // stage st+1, held in registers, is written to the other buffer (its previous
 // contents were last read before the barrier that ended stage st-1); then
-// stage st+2 is fetched into the registers.  Loads go through buffer
+// stage st+2 is fetched into the registers (with two stages in registers,
+// for grids too small to cover the loads' latency, stage st+3).  Loads go through buffer
 // descriptors (scalar base and size, a 32-bit offset per load).  Scale bytes
 // arrive 16 per row every four stages (a 4-byte fetch per row and stage costs
 // a whole L2 request for 4 useful bytes).  Inside LDS the 16-byte chunks of a
@@ -974,7 +975,8 @@ static int64_t big_tile_rows(int64_t M, int64_t N) {
   return rows > 0 ? rows : ntm;
 }
 
-// rows -> tile shape, for the product with or without a map.
+// Calls go(tile, first row, rows) for the tile shapes that M x N takes, with or
+// without a map.
 template <class Go>
 static hipError_t on_tiles(int64_t M, int64_t N, Go go) {
   if (use_tall_tiles(M, N)) return go(Tall{}, 0, M);
