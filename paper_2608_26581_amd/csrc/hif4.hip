@@ -42,9 +42,9 @@
 //
 // Quantizer work decomposition: a lane owns 8 consecutive elements (one
 // 8-element group, 16 bytes of bf16 or 32 of fp32 input); the 8 lanes of a
-// block combine their maxima and metadata bits with DPP; a wave covers 32
-// blocks in 4 steps, each load instruction reading 1 KB (bf16) of contiguous
-// input and each code store writing 256 contiguous bytes.
+// block combine their maxima and metadata bits with DPP; each load instruction
+// of a wave reads 1 KB (bf16) of contiguous input and each code store writes
+// 256 contiguous bytes.
 //
 // Product.  gfx950 has no matrix-core format for HiF4, so the product
 // decodes codes to bf16 and runs v_mfma_f32_32x32x16_bf16, whose products are
@@ -77,10 +77,14 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 constexpr int kH = 64;                 // elements per HiF4 block
 constexpr int kQThreads = 256;
-constexpr int kQSteps = 4;             // 8-element units per lane (large tensors)
-// Below this many 8-element units a lane takes one unit, so that small
-// (decode-sized) tensors spread over four times as many waves.
-constexpr int64_t kQSmallUnits = int64_t(1) << 18;
+// A lane takes one 8-element unit: the kernel is bound by instruction issue,
+// so as many waves as there are hide each other best.  Measured (bf16 input with
+// the residual, one unit / four units per lane): 64 rows x 4096 2.7 / 5.5 us, 300
+// x 13824 6.9 / 8.3, 2000 x 4096 11.0 / 12.8, 4096 x 4096 19.4 / 21.0, 8192 x 4096
+// 34.1 / 35.5; fp32 weights 12288 x 4096 40.9 / 43.6; two units lie between.  Four
+// from where a lane per unit would pass a launch's 2^32 work items.
+constexpr int kQSteps = 4;
+constexpr int64_t kQSmallUnits = (int64_t(1) << 32) - kQThreads;
 constexpr int kLoopGrid = 1 << 16;     // dequantization grid cap (loops over the rest)
 
 // Every lane of these permutations has a source, so the old value never
