@@ -412,9 +412,9 @@ rfq_status rfq_hif4_gemm_wbf16(const uint8_t *q_codes, const uint32_t *q_meta,
  * the few-row product's grid leaves its last round of workgroups partly
  * empty (e.g. N = 5120), that product split over K in 2 to 4 parts.  From
  * 1024 rows, where K is not split, the workspace instead receives the
- * weights decoded to bf16 (N * K * 2 bytes, at most 1 GiB) and the product
- * of rfq_hif4_gemm_wbf16 runs on them: the bits of rfq_hif4_gemm, without
- * decoding W again for every 128 rows.
+ * weights decoded to bf16 (N * K * 2 bytes, at most 1 GiB, in an order of the
+ * library's own) and is multiplied from there: the bits of rfq_hif4_gemm,
+ * without decoding W again for every 128 rows.
  * Each part of K writes its fp32 partial
  * sums to the workspace; one pass then adds the parts in a fixed order and
  * rounds to z_dtype, so the result is deterministic but its fp32 summation

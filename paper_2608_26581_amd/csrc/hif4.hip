@@ -1552,11 +1552,11 @@ static bool split_on_tiles(int64_t M, int64_t N, int64_t K, const SplitPlan &til
 }
 
 // Without a split, from this many rows the weights are decoded to bf16 once
-// into the workspace and the bf16-weight product runs on them (the same bits
-// as the codes form, whose tile rows each decode all of W again).  Measured
-// (bf16 Z, decode included): 4096 rows x 4096 x 12288 832 -> 740 us, 4096 x
-// 12288 x 4096 847 -> 754-780, 4096 x 13824 x 5120 1218 -> 1084-1100, 1024
-// rows x 12288 x 4096 268 -> 249; at 512 rows no gain (220 against 228).
+// into the workspace, in operand order (N a multiple of 32) or row by row for
+// the bf16-weight product (the same bits as the codes form, whose tile rows
+// each decode all of W again).  Measured, bf16 Z, decode included: 4096 rows x
+// 12288 x 4096 799 -> 617 us, row by row 747; when the line was drawn, row by
+// row: 1024 rows x 12288 x 4096 268 -> 249, at 512 rows no gain (220 / 228).
 constexpr int64_t kDecodeMinRows = 1024;
 constexpr int64_t kDecodeMaxBytes = int64_t(1) << 30;
 
