@@ -36,6 +36,7 @@ def build_calls(verbose=False):
            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
            "-isystem", "/opt/rocm/include", "-I", sysconfig.get_paths()["include"],
+           "-I", os.path.join(REPO_DIR, "include"),
            os.path.join(PKG_DIR, "csrc_host", "calls.cpp"), "-o", tmp,
            "-L", os.path.join(root, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
     if verbose:

@@ -6,8 +6,9 @@
 // a call, 14 with a workspace).  Each function here takes the binding's
 // arguments and returns its result, or None where anything is not the common
 // form (a tensor subclass, another device, a wrong shape or type) or the
-// library returned an error: the caller then goes through the Python path,
-// which accepts the rest and words the errors.
+// library refused an argument: the caller then goes through the Python path,
+// which accepts the rest and words the errors.  Any other failure comes back
+// as the library's status and is not tried again.
 #include <Python.h>
 
 #include <ATen/ATen.h>
@@ -17,6 +18,8 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
+
+#include "rfq.h"
 
 namespace {
 
@@ -68,6 +71,16 @@ at::Tensor empty(const at::Tensor &like, int64_t rows, int64_t cols, at::ScalarT
 void *stream_of(int dev) { return c10::hip::getCurrentHIPStream((c10::DeviceIndex)dev).stream(); }
 
 PyObject *none() { Py_RETURN_NONE; }
+
+// What a call returns for status st other than RFQ_OK.  The argument errors
+// are found on the host before anything runs; after a failed launch part of
+// the call may have run, and the launch's error has been read (and so
+// cleared), so that a second try could report success.
+PyObject *failed(int st) {
+  const bool argument = st == RFQ_ERR_NULL || st == RFQ_ERR_SHAPE || st == RFQ_ERR_DTYPE ||
+                        st == RFQ_ERR_ALIGN;
+  return argument ? none() : PyLong_FromLong(st);
+}
 
 // The current device, or -1 where o is not a device tensor.
 int device_for(PyObject *o) {
@@ -127,8 +140,7 @@ PyObject *quantize(PyObject *, PyObject *const *a, Py_ssize_t n) {
   for (int i = 0; i < 4; ++i) p[i] = t[i].defined() ? t[i].data_ptr() : nullptr;
   const int st = (HIF4 ? lib.hif4_quantize : lib.quantize_act)(
       x->data_ptr(), float_code(*x), rows, K, p[0], p[1], p[2], p[3], stream_of(dev));
-  if (st) return none();
-  return tuple(t, 4);
+  return st ? failed(st) : tuple(t, 4);
   END_HANDLE_TH_ERRORS
 }
 
@@ -194,7 +206,7 @@ PyObject *gemm(PyObject *, PyObject *const *a, Py_ssize_t n) {
                                            p.M, p.N, p.K, z.data_ptr(), float_code(z),
                                            stream_of(dev));
   }
-  return st ? none() : result(a[7], z);
+  return st ? failed(st) : result(a[7], z);
   END_HANDLE_TH_ERRORS
 }
 
@@ -217,7 +229,7 @@ PyObject *gemm_phi(PyObject *, PyObject *const *a, Py_ssize_t n) {
   const int st = lib.gemm_phi(p.q.c(), p.q.s(), p.r.c(), p.r.s(), p.w.c(), p.w.s(),
                               phi ? phi->data_ptr() : nullptr, p.M, p.N, p.K, z.data_ptr(),
                               float_code(z), stream_of(dev));
-  return st ? none() : result(a[8], z);
+  return st ? failed(st) : result(a[8], z);
   END_HANDLE_TH_ERRORS
 }
 
@@ -244,7 +256,7 @@ PyObject *fallback_map(PyObject *, PyObject *const *a, Py_ssize_t n) {
   const at::Tensor phi = empty(*qs, (M + 63) / 64, (K + 255) / 256, at::kByte);
   const int st = lib.fallback_map(r ? r->data_ptr() : nullptr, qs->data_ptr(), M, K, (int)rule,
                                   (int)threshold, phi.data_ptr(), stream_of(dev));
-  return st ? none() : THPVariable_Wrap(phi);
+  return st ? failed(st) : THPVariable_Wrap(phi);
   END_HANDLE_TH_ERRORS
 }
 
@@ -268,7 +280,7 @@ PyObject *gemm_swiglu_quantize(PyObject *, PyObject *const *a, Py_ssize_t n) {
       p.q.c(), p.q.s(), p.r.c(), p.r.s(), p.w.c(), p.w.s(), p.M, Nh, p.K, t[0].data_ptr(),
       t[1].data_ptr(), residual ? t[2].data_ptr() : nullptr, residual ? t[3].data_ptr() : nullptr,
       nullptr, stream_of(dev));
-  return st ? none() : tuple(t, 5);
+  return st ? failed(st) : tuple(t, 5);
   END_HANDLE_TH_ERRORS
 }
 
@@ -289,7 +301,7 @@ PyObject *gemm_stream(PyObject *, PyObject *const *a, Py_ssize_t n) {
   if (!z.defined()) return none();
   const int st = lib.gemm_stream(x->data_ptr(), float_code(*x), residual, ow.c(), ow.s(), M, N, K,
                                  z.data_ptr(), float_code(z), stream_of(dev));
-  return st ? none() : result(a[5], z);
+  return st ? failed(st) : result(a[5], z);
   END_HANDLE_TH_ERRORS
 }
 

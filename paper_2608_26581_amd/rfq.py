@@ -111,6 +111,15 @@ def load():
     return lib
 
 
+# The entry points that the native calls use, in the order their bind() takes.
+_NATIVE_ENTRIES = (
+    "rfq_quantize_act", "rfq_gemm", "rfq_gemm_split", "rfq_gemm_workspace_bytes",
+    "rfq_gemm_stream", "rfq_hif4_quantize", "rfq_hif4_gemm", "rfq_hif4_gemm_split",
+    "rfq_hif4_gemm_workspace_bytes", "rfq_gemm_phi", "rfq_fallback_map",
+    "rfq_gemm_swiglu_quantize",
+)
+
+
 def _bind_calls(lib):
     """Loads the native calls once and points them at lib's entry points."""
     global _calls
@@ -121,11 +130,7 @@ def _bind_calls(lib):
         spec = importlib.util.spec_from_file_location("_rfq_calls", CALLS_PATH)
         _calls = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(_calls)
-    _calls.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
-        lib.rfq_quantize_act, lib.rfq_gemm, lib.rfq_gemm_split, lib.rfq_gemm_workspace_bytes,
-        lib.rfq_gemm_stream, lib.rfq_hif4_quantize, lib.rfq_hif4_gemm, lib.rfq_hif4_gemm_split,
-        lib.rfq_hif4_gemm_workspace_bytes, lib.rfq_gemm_phi, lib.rfq_fallback_map,
-        lib.rfq_gemm_swiglu_quantize)))
+    _calls.bind(*(ctypes.cast(getattr(lib, f), ctypes.c_void_p).value for f in _NATIVE_ENTRIES))
 
 
 # dtype codes of out_dtype for the native calls (others: checked in Python).
@@ -133,10 +138,15 @@ _OUT_CODE = {torch.float32: RFQ_F32, torch.bfloat16: RFQ_BF16}
 
 
 def _native(func, *args):
-    """The result of a native call, or None where the Python path takes over."""
+    """The result of a native call, or None where the Python path takes over.
+    A status (a failed launch, not a refused argument) is raised here: the call
+    is not made a second time."""
     if _calls is None:
         load()
-    return getattr(_calls, func)(*args)
+    r = getattr(_calls, func)(*args)
+    if type(r) is int:
+        raise RfqError("rfq_" + func, r)
+    return r
 
 
 def rfq_status_str(status):

@@ -1,10 +1,14 @@
 """The binding's native calls against its Python path: the same results (an
 explicit stream argument takes the Python path), the same objects where `out`
-is given, and the same errors for arguments that are not the common form."""
+is given, and the same errors for arguments that are not the common form.
+A failed launch is raised and the call not made a second time."""
+import ctypes
+
 import pytest
 import torch
 
 import paper_2608_26581_amd as rfq
+from paper_2608_26581_amd import rfq as binding
 
 pytestmark = pytest.mark.gpu
 
@@ -78,3 +82,62 @@ def test_native_calls_refuse_what_the_python_path_refuses():
         rfq.rfq_quantize_act(x[:, :40].contiguous())
     with pytest.raises(TypeError):
         rfq.rfq_quantize_act(x.half())
+
+
+def _operands():
+    x = torch.randn(40, 2048, device="cuda")
+    w = torch.randn(96, 2048, device="cuda")
+    return (x, rfq.rfq_quantize_act(x), rfq.rfq_quantize_weight(w), rfq.rfq_hif4_quantize(x),
+            rfq.rfq_hif4_quantize(w, residual=False)[:2])
+
+
+def _common_forms():
+    """name in the native module -> a call of the binding in that form."""
+    x, q, w, h, hw = _operands()
+    phi = rfq.rfq_fallback_map(q[2], q[1], 0)
+    return {
+        "quantize_act": lambda: rfq.rfq_quantize_act(x),
+        "hif4_quantize": lambda: rfq.rfq_hif4_quantize(x),
+        "gemm": lambda: rfq.rfq_gemm(*q, *w),
+        "gemm, split": lambda: rfq.rfq_gemm(*q, *w, split=True),
+        "hif4_gemm": lambda: rfq.rfq_hif4_gemm(*h, *hw),
+        "hif4_gemm, split": lambda: rfq.rfq_hif4_gemm(*h, *hw, split=True),
+        "gemm_stream": lambda: rfq.rfq_gemm_stream(x, *w),
+        "gemm_phi": lambda: rfq.rfq_gemm_phi(*q, *w, phi),
+        "fallback_map": lambda: rfq.rfq_fallback_map(q[2], q[1], 0),
+        "gemm_swiglu_quantize": lambda: rfq.rfq_gemm_swiglu_quantize(*q, w[0][:64], w[1][:64]),
+    }
+
+
+def _bind_stub(stub):
+    """Points the native calls at stub, except for the workspace sizes."""
+    lib = binding.load()
+    address = ctypes.cast(stub, ctypes.c_void_p).value
+    binding._calls.bind(*(
+        ctypes.cast(getattr(lib, f), ctypes.c_void_p).value if f.endswith("_bytes") else address
+        for f in binding._NATIVE_ENTRIES))
+
+
+def test_a_failed_launch_is_raised_and_the_call_not_repeated(monkeypatch):
+    launches = []
+    stub = ctypes.CFUNCTYPE(ctypes.c_int)(lambda: launches.append(1) or 6)   # RFQ_ERR_LAUNCH
+    forms, lib = _common_forms(), binding.load()
+
+    class StatusNamesOnly:
+        rfq_status_str = lib.rfq_status_str
+        rfq_gemm_workspace_bytes = lib.rfq_gemm_workspace_bytes
+        rfq_hif4_gemm_workspace_bytes = lib.rfq_hif4_gemm_workspace_bytes
+
+        def __getattr__(self, name):
+            raise AssertionError("%s called after the failed launch" % name)
+
+    monkeypatch.setattr(binding, "_lib", StatusNamesOnly())
+    _bind_stub(stub)
+    try:
+        for name, call in forms.items():
+            launches.clear()
+            with pytest.raises(rfq.RfqError, match="RFQ_ERR_LAUNCH") as e:
+                call()
+            assert e.value.status == 6 and len(launches) == 1, name
+    finally:
+        binding._bind_calls(lib)
