@@ -64,8 +64,31 @@ int float_code(const at::Tensor &t) {
   return t.scalar_type() == at::kBFloat16 ? 1 : (t.scalar_type() == at::kFloat ? 0 : -1);
 }
 
-at::Tensor empty(const at::Tensor &like, int64_t rows, int64_t cols, at::ScalarType type) {
-  return at::empty({rows, cols}, like.options().dtype(type).requires_grad(false));
+// Releases the interpreter lock for its lifetime: an allocation may have to
+// wait for the driver and a launch for room in a full queue, and a host
+// callback that the queue waits for may need the lock.
+class NoGil {
+ public:
+  NoGil() : state_(PyEval_SaveThread()) {}
+  ~NoGil() { PyEval_RestoreThread(state_); }
+  NoGil(const NoGil &) = delete;
+  NoGil &operator=(const NoGil &) = delete;
+
+ private:
+  PyThreadState *state_;
+};
+
+// A new tensor on like's device (called without the interpreter lock).
+at::Tensor empty(const at::Tensor &like, at::IntArrayRef sizes, at::ScalarType type) {
+  return at::empty(sizes, like.options().dtype(type).requires_grad(false));
+}
+
+// A library call without the interpreter lock; its arguments are read from
+// the tensors before.
+template <class F, class... A>
+int call(F f, A... a) {
+  const NoGil unlocked;
+  return f(a...);
 }
 
 void *stream_of(int dev) { return c10::hip::getCurrentHIPStream((c10::DeviceIndex)dev).stream(); }
@@ -132,14 +155,17 @@ PyObject *quantize(PyObject *, PyObject *const *a, Py_ssize_t n) {
   if (residual < 0) return nullptr;
   const int64_t rows = x->size(0), K = x->size(1);
   at::Tensor t[4];
-  for (int i = 0; i < (residual ? 4 : 2); i += 2) {
-    t[i] = empty(*x, rows, K / 2, at::kByte);
-    t[i + 1] = HIF4 ? empty(*x, rows, K / 64, at::kInt) : empty(*x, rows, K / 32, at::kByte);
+  {
+    const NoGil unlocked;
+    for (int i = 0; i < (residual ? 4 : 2); i += 2) {
+      t[i] = empty(*x, {rows, K / 2}, at::kByte);
+      t[i + 1] = HIF4 ? empty(*x, {rows, K / 64}, at::kInt) : empty(*x, {rows, K / 32}, at::kByte);
+    }
   }
   void *p[4];
   for (int i = 0; i < 4; ++i) p[i] = t[i].defined() ? t[i].data_ptr() : nullptr;
-  const int st = (HIF4 ? lib.hif4_quantize : lib.quantize_act)(
-      x->data_ptr(), float_code(*x), rows, K, p[0], p[1], p[2], p[3], stream_of(dev));
+  const int st = call(HIF4 ? lib.hif4_quantize : lib.quantize_act, x->data_ptr(), float_code(*x),
+                      rows, K, p[0], p[1], p[2], p[3], stream_of(dev));
   return st ? failed(st) : tuple(t, 4);
   END_HANDLE_TH_ERRORS
 }
@@ -152,7 +178,8 @@ at::Tensor output(PyObject *out, int code, const at::Tensor &like, int64_t M, in
     return t && float_code(*t) >= 0 && t->size(0) == M && t->size(1) == N ? *t : at::Tensor();
   }
   if (code != 0 && code != 1) return at::Tensor();
-  return empty(like, M, N, code ? at::kBFloat16 : at::kFloat);
+  const NoGil unlocked;
+  return empty(like, {M, N}, code ? at::kBFloat16 : at::kFloat);
 }
 
 // What a call with `out` returns: that object, or the new tensor.
@@ -197,14 +224,17 @@ PyObject *gemm(PyObject *, PyObject *const *a, Py_ssize_t n) {
     bytes = (HIF4 ? lib.hif4_gemm_workspace_bytes : lib.gemm_workspace_bytes)(p.M, p.N, p.K);
   int st;
   if (bytes > 0) {
-    const at::Tensor work = at::empty({bytes}, p.q.codes->options());
-    st = (HIF4 ? lib.hif4_gemm_split : lib.gemm_split)(
-        p.q.c(), p.q.s(), p.r.c(), p.r.s(), p.w.c(), p.w.s(), p.M, p.N, p.K, z.data_ptr(),
-        float_code(z), work.data_ptr(), bytes, stream_of(dev));
+    at::Tensor work;
+    {
+      const NoGil unlocked;
+      work = empty(*p.q.codes, {bytes}, at::kByte);
+    }
+    st = call(HIF4 ? lib.hif4_gemm_split : lib.gemm_split, p.q.c(), p.q.s(), p.r.c(), p.r.s(),
+              p.w.c(), p.w.s(), p.M, p.N, p.K, z.data_ptr(), float_code(z), work.data_ptr(),
+              bytes, stream_of(dev));
   } else {
-    st = (HIF4 ? lib.hif4_gemm : lib.gemm)(p.q.c(), p.q.s(), p.r.c(), p.r.s(), p.w.c(), p.w.s(),
-                                           p.M, p.N, p.K, z.data_ptr(), float_code(z),
-                                           stream_of(dev));
+    st = call(HIF4 ? lib.hif4_gemm : lib.gemm, p.q.c(), p.q.s(), p.r.c(), p.r.s(), p.w.c(),
+              p.w.s(), p.M, p.N, p.K, z.data_ptr(), float_code(z), stream_of(dev));
   }
   return st ? failed(st) : result(a[7], z);
   END_HANDLE_TH_ERRORS
@@ -226,9 +256,9 @@ PyObject *gemm_phi(PyObject *, PyObject *const *a, Py_ssize_t n) {
   if (code == -1 && PyErr_Occurred()) return nullptr;
   const at::Tensor z = output(a[8], (int)code, *p.q.codes, p.M, p.N, dev);
   if (!z.defined()) return none();
-  const int st = lib.gemm_phi(p.q.c(), p.q.s(), p.r.c(), p.r.s(), p.w.c(), p.w.s(),
-                              phi ? phi->data_ptr() : nullptr, p.M, p.N, p.K, z.data_ptr(),
-                              float_code(z), stream_of(dev));
+  const int st = call(lib.gemm_phi, p.q.c(), p.q.s(), p.r.c(), p.r.s(), p.w.c(), p.w.s(),
+                      phi ? phi->data_ptr() : nullptr, p.M, p.N, p.K, z.data_ptr(), float_code(z),
+                      stream_of(dev));
   return st ? failed(st) : result(a[8], z);
   END_HANDLE_TH_ERRORS
 }
@@ -253,9 +283,13 @@ PyObject *fallback_map(PyObject *, PyObject *const *a, Py_ssize_t n) {
   const long threshold = over ? 0 : PyLong_AsLongAndOverflow(a[3], &over);
   if (over || (rule != 0 && rule != 1) || threshold != (int)threshold || (rule == 0 && !r))
     return none();
-  const at::Tensor phi = empty(*qs, (M + 63) / 64, (K + 255) / 256, at::kByte);
-  const int st = lib.fallback_map(r ? r->data_ptr() : nullptr, qs->data_ptr(), M, K, (int)rule,
-                                  (int)threshold, phi.data_ptr(), stream_of(dev));
+  at::Tensor phi;
+  {
+    const NoGil unlocked;
+    phi = empty(*qs, {(M + 63) / 64, (K + 255) / 256}, at::kByte);
+  }
+  const int st = call(lib.fallback_map, r ? r->data_ptr() : nullptr, qs->data_ptr(), M, K,
+                      (int)rule, (int)threshold, phi.data_ptr(), stream_of(dev));
   return st ? failed(st) : THPVariable_Wrap(phi);
   END_HANDLE_TH_ERRORS
 }
@@ -272,14 +306,17 @@ PyObject *gemm_swiglu_quantize(PyObject *, PyObject *const *a, Py_ssize_t n) {
   if (residual < 0) return nullptr;
   const int64_t Nh = p.N / 2;
   at::Tensor t[5];
-  for (int i = 0; i < (residual ? 4 : 2); i += 2) {
-    t[i] = empty(*p.q.codes, p.M, Nh / 2, at::kByte);
-    t[i + 1] = empty(*p.q.codes, p.M, Nh / 32, at::kByte);
+  {
+    const NoGil unlocked;
+    for (int i = 0; i < (residual ? 4 : 2); i += 2) {
+      t[i] = empty(*p.q.codes, {p.M, Nh / 2}, at::kByte);
+      t[i + 1] = empty(*p.q.codes, {p.M, Nh / 32}, at::kByte);
+    }
   }
-  const int st = lib.gemm_swiglu_quantize(
-      p.q.c(), p.q.s(), p.r.c(), p.r.s(), p.w.c(), p.w.s(), p.M, Nh, p.K, t[0].data_ptr(),
-      t[1].data_ptr(), residual ? t[2].data_ptr() : nullptr, residual ? t[3].data_ptr() : nullptr,
-      nullptr, stream_of(dev));
+  const int st = call(lib.gemm_swiglu_quantize, p.q.c(), p.q.s(), p.r.c(), p.r.s(), p.w.c(),
+                      p.w.s(), p.M, Nh, p.K, t[0].data_ptr(), t[1].data_ptr(),
+                      residual ? t[2].data_ptr() : nullptr, residual ? t[3].data_ptr() : nullptr,
+                      nullptr, stream_of(dev));
   return st ? failed(st) : tuple(t, 5);
   END_HANDLE_TH_ERRORS
 }
@@ -299,8 +336,8 @@ PyObject *gemm_stream(PyObject *, PyObject *const *a, Py_ssize_t n) {
   if (residual < 0 || (code == -1 && PyErr_Occurred())) return nullptr;
   const at::Tensor z = output(a[5], (int)code, *x, M, N, dev);
   if (!z.defined()) return none();
-  const int st = lib.gemm_stream(x->data_ptr(), float_code(*x), residual, ow.c(), ow.s(), M, N, K,
-                                 z.data_ptr(), float_code(z), stream_of(dev));
+  const int st = call(lib.gemm_stream, x->data_ptr(), float_code(*x), residual, ow.c(), ow.s(), M,
+                      N, K, z.data_ptr(), float_code(z), stream_of(dev));
   return st ? failed(st) : result(a[5], z);
   END_HANDLE_TH_ERRORS
 }

@@ -1,7 +1,8 @@
 """The binding's native calls against its Python path: the same results (an
 explicit stream argument takes the Python path), the same objects where `out`
 is given, and the same errors for arguments that are not the common form.
-A failed launch is raised and the call not made a second time."""
+A failed launch is raised and the call not made a second time, and the
+interpreter lock is released around the library."""
 import ctypes
 
 import pytest
@@ -139,5 +140,28 @@ def test_a_failed_launch_is_raised_and_the_call_not_repeated(monkeypatch):
             with pytest.raises(rfq.RfqError, match="RFQ_ERR_LAUNCH") as e:
                 call()
             assert e.value.status == 6 and len(launches) == 1, name
+    finally:
+        binding._bind_calls(lib)
+
+
+def test_the_interpreter_lock_is_released_around_the_library():
+    """The library's entry points stand for PyGILState_Check here: it returns 1
+    (an argument error to the native call, which then gives None) where the
+    thread holds the lock and 0 (done: the result) where it does not."""
+    forms, lib, native = _common_forms(), binding.load(), {}
+
+    def only_native(func, *args):
+        native[func] = getattr(binding._calls, func)(*args)
+        raise StopIteration
+
+    _bind_stub(ctypes.pythonapi.PyGILState_Check)
+    try:
+        with pytest.MonkeyPatch.context() as m:
+            m.setattr(binding, "_native", only_native)
+            for name, call in forms.items():
+                native.clear()
+                with pytest.raises(StopIteration):
+                    call()
+                assert list(native.values())[0] is not None, name
     finally:
         binding._bind_calls(lib)
