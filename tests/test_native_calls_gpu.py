@@ -92,22 +92,71 @@ def _operands():
             rfq.rfq_hif4_quantize(w, residual=False)[:2])
 
 
-def _common_forms():
-    """name in the native module -> a call of the binding in that form."""
+def _common_forms(wrap=lambda t: t, **kw):
+    """name in the native module -> a call of the binding in that form, with
+    every tensor passed through wrap."""
     x, q, w, h, hw = _operands()
     phi = rfq.rfq_fallback_map(q[2], q[1], 0)
+    x, phi = wrap(x), wrap(phi)
+    q, w, h, hw = (tuple(map(wrap, t)) for t in (q, w, h, hw))
     return {
-        "quantize_act": lambda: rfq.rfq_quantize_act(x),
-        "hif4_quantize": lambda: rfq.rfq_hif4_quantize(x),
-        "gemm": lambda: rfq.rfq_gemm(*q, *w),
-        "gemm, split": lambda: rfq.rfq_gemm(*q, *w, split=True),
-        "hif4_gemm": lambda: rfq.rfq_hif4_gemm(*h, *hw),
-        "hif4_gemm, split": lambda: rfq.rfq_hif4_gemm(*h, *hw, split=True),
-        "gemm_stream": lambda: rfq.rfq_gemm_stream(x, *w),
-        "gemm_phi": lambda: rfq.rfq_gemm_phi(*q, *w, phi),
-        "fallback_map": lambda: rfq.rfq_fallback_map(q[2], q[1], 0),
-        "gemm_swiglu_quantize": lambda: rfq.rfq_gemm_swiglu_quantize(*q, w[0][:64], w[1][:64]),
+        "quantize_act": lambda: rfq.rfq_quantize_act(x, **kw),
+        "hif4_quantize": lambda: rfq.rfq_hif4_quantize(x, **kw),
+        "gemm": lambda: rfq.rfq_gemm(*q, *w, **kw),
+        "gemm, split": lambda: rfq.rfq_gemm(*q, *w, split=True, **kw),
+        "hif4_gemm": lambda: rfq.rfq_hif4_gemm(*h, *hw, **kw),
+        "hif4_gemm, split": lambda: rfq.rfq_hif4_gemm(*h, *hw, split=True, **kw),
+        "gemm_stream": lambda: rfq.rfq_gemm_stream(x, *w, **kw),
+        "gemm_phi": lambda: rfq.rfq_gemm_phi(*q, *w, phi, **kw),
+        "fallback_map": lambda: rfq.rfq_fallback_map(q[2], q[1], 0, **kw),
+        "gemm_swiglu_quantize": lambda: rfq.rfq_gemm_swiglu_quantize(*q, w[0][:64], w[1][:64], **kw),
     }
+
+
+def _native_result(monkeypatch, call):
+    """What the native call returns to the binding."""
+    class Done(Exception):
+        pass
+
+    got = []
+
+    def native(func, *args):
+        got.append(getattr(binding._calls, func)(*args))
+        raise Done
+
+    with monkeypatch.context() as m:
+        m.setattr(binding, "_native", native)
+        with pytest.raises(Done):
+            call()
+    return got[0]
+
+
+def test_the_common_forms_are_served_natively(monkeypatch):
+    """Every common form gets its result from the native call, also on another
+    stream: with nothing native the binding would still answer, in Python."""
+    torch.manual_seed(7)
+    forms = _common_forms()
+    torch.manual_seed(7)
+    python = _common_forms(stream=torch.cuda.current_stream())
+    side = torch.cuda.Stream()
+    for name, call in forms.items():
+        r = _native_result(monkeypatch, call)
+        assert r is not None, name
+        _same(r, python[name]())
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            s = _native_result(monkeypatch, call)
+        torch.cuda.current_stream().wait_stream(side)
+        _same(s, r)
+
+
+@pytest.mark.parametrize("wrap", [lambda t: t.as_subclass(Sub), lambda t: t.cpu(),
+                                  lambda t: t[:, :-1], lambda t: t.float() if t.dtype in (
+                                      torch.uint8, torch.int32) else t.half()],
+                         ids=["subclass", "cpu", "narrowed", "dtype"])
+def test_other_forms_are_left_to_the_python_path(monkeypatch, wrap):
+    for name, call in _common_forms(wrap).items():
+        assert _native_result(monkeypatch, call) is None, name
 
 
 def _bind_stub(stub):
@@ -144,24 +193,14 @@ def test_a_failed_launch_is_raised_and_the_call_not_repeated(monkeypatch):
         binding._bind_calls(lib)
 
 
-def test_the_interpreter_lock_is_released_around_the_library():
+def test_the_interpreter_lock_is_released_around_the_library(monkeypatch):
     """The library's entry points stand for PyGILState_Check here: it returns 1
     (an argument error to the native call, which then gives None) where the
     thread holds the lock and 0 (done: the result) where it does not."""
-    forms, lib, native = _common_forms(), binding.load(), {}
-
-    def only_native(func, *args):
-        native[func] = getattr(binding._calls, func)(*args)
-        raise StopIteration
-
+    forms, lib = _common_forms(), binding.load()
     _bind_stub(ctypes.pythonapi.PyGILState_Check)
     try:
-        with pytest.MonkeyPatch.context() as m:
-            m.setattr(binding, "_native", only_native)
-            for name, call in forms.items():
-                native.clear()
-                with pytest.raises(StopIteration):
-                    call()
-                assert list(native.values())[0] is not None, name
+        for name, call in forms.items():
+            assert _native_result(monkeypatch, call) is not None, name
     finally:
         binding._bind_calls(lib)
