@@ -5,6 +5,7 @@ import os
 import subprocess
 import sysconfig
 import tempfile
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
@@ -12,6 +13,7 @@ REPO_DIR = os.path.dirname(PKG_DIR)
 LIB_PATH = os.path.join(PKG_DIR, "librfq.so")
 CALLS_PATH = os.path.join(PKG_DIR, "_rfq_calls.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+CXX = os.environ.get("CXX", "g++")
 
 # -packed-fp32-ops: no packed fp32 VALU instructions are generated.
 FLAGS = [
@@ -31,7 +33,8 @@ def build_calls(verbose=False):
     root = os.path.dirname(torch.__file__)
     inc = os.path.join(root, "include")
     tmp = CALLS_PATH + ".tmp"
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+    cmd = [CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           '-DRFQ_TORCH_VERSION="%s"' % torch.__version__,
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
@@ -46,6 +49,19 @@ def build_calls(verbose=False):
         raise RuntimeError("_rfq_calls build failed:\n" + res.stderr)
     os.replace(tmp, CALLS_PATH)
     return CALLS_PATH
+
+
+def build_calls_if_possible(verbose=False):
+    """build_calls, or a warning and no module where it does not compile here (no
+    g++, torch headers that do not fit): librfq does not need it."""
+    try:
+        return build_calls(verbose)
+    except (ImportError, OSError, RuntimeError) as e:
+        if os.path.exists(CALLS_PATH):
+            os.remove(CALLS_PATH)
+        warnings.warn("the binding's native calls are not built, it makes its calls in Python: %s"
+                      % e, RuntimeWarning, stacklevel=2)
+        return None
 
 
 def build(verbose=False, extra_flags=(), out=LIB_PATH):
@@ -73,7 +89,7 @@ def build(verbose=False, extra_flags=(), out=LIB_PATH):
         run([HIPCC, *flags, "-shared", *pool.map(compile_one, sources()), "-o", tmp])
     os.replace(tmp, out)
     if out == LIB_PATH:
-        build_calls(verbose)
+        build_calls_if_possible(verbose)
     return out
 
 

@@ -377,4 +377,14 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_rfq_calls", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__rfq_calls() { return PyModule_Create(&module); }
+// torch_version: the torch that the module was compiled against (its C++
+// interface changes between versions; the binding uses the module only with
+// the same one).
+PyMODINIT_FUNC PyInit__rfq_calls() {
+  PyObject *m = PyModule_Create(&module);
+  if (m && PyModule_AddStringConstant(m, "torch_version", RFQ_TORCH_VERSION) < 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

@@ -12,6 +12,7 @@ not passed in.
 import ctypes
 import importlib.util
 import os
+import warnings
 
 import torch
 
@@ -50,7 +51,8 @@ RFQ_PHI_SCALE_AT_LEAST = 1
 
 _lib = None
 # The native calls (csrc_host/calls.cpp): the functions below hand them their
-# arguments first and go on in Python where they return None.
+# arguments first and go on in Python where they return None.  False where the
+# module cannot be used: every call then goes through Python.
 _calls = None
 
 
@@ -120,16 +122,32 @@ _NATIVE_ENTRIES = (
 )
 
 
+def _load_calls():
+    """The native calls' module, or False with a warning where it is not built
+    or not for this torch: librfq itself needs neither g++ nor torch's C++
+    interface, and the Python path makes every call."""
+    try:
+        if not os.path.exists(CALLS_PATH):
+            raise ImportError("not built (__graft_entry__.build() builds it)")
+        spec = importlib.util.spec_from_file_location("_rfq_calls", CALLS_PATH)
+        calls = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(calls)
+        if calls.torch_version != torch.__version__:
+            raise ImportError("built against torch %s" % calls.torch_version)
+        return calls
+    except ImportError as e:
+        warnings.warn("%s cannot be used, calls take 9-14 us of host time instead of 4-7: %s"
+                      % (CALLS_PATH, e), RuntimeWarning, stacklevel=2)
+        return False
+
+
 def _bind_calls(lib):
     """Loads the native calls once and points them at lib's entry points."""
     global _calls
     if _calls is None:
-        if not os.path.exists(CALLS_PATH):
-            raise RuntimeError("_rfq_calls.so is not built (expected at %s); run "
-                               "__graft_entry__.build()" % CALLS_PATH)
-        spec = importlib.util.spec_from_file_location("_rfq_calls", CALLS_PATH)
-        _calls = importlib.util.module_from_spec(spec)
-        spec.loader.exec_module(_calls)
+        _calls = _load_calls()
+    if not _calls:
+        return
     _calls.bind(*(ctypes.cast(getattr(lib, f), ctypes.c_void_p).value for f in _NATIVE_ENTRIES))
 
 
@@ -143,6 +161,8 @@ def _native(func, *args):
     is not made a second time."""
     if _calls is None:
         load()
+    if not _calls:
+        return None
     r = getattr(_calls, func)(*args)
     if type(r) is int:
         raise RfqError("rfq_" + func, r)
