@@ -1,0 +1,42 @@
+"""Where a product's store width or kernel changes with its sizes: the results on
+both sides of the line."""
+import pytest
+import torch
+
+import paper_2608_26581_amd as rfq
+
+pytestmark = pytest.mark.gpu
+
+
+def _mx(M, N, K, seed=0):
+    gen = torch.Generator(device="cuda").manual_seed(seed + M + N + K)
+    x = torch.randn((M, K), generator=gen, device="cuda")
+    x[:, ::37] *= 40
+    w = torch.randn((N, K), generator=gen, device="cuda") * 0.02
+    return rfq.rfq_quantize_act(x), rfq.rfq_quantize_weight(w)
+
+
+def _guarded(M, N, dtype):
+    """An [M][N] tensor and a check that the 256 bytes on either side of it
+    stayed as they were."""
+    n = M * N * (2 if dtype == torch.bfloat16 else 4)
+    raw = torch.full((n + 512,), 0x5A, dtype=torch.uint8, device="cuda")
+    return raw[256:256 + n].view(dtype).view(M, N), lambda: bool(
+        (raw[:256] == 0x5A).all() and (raw[256 + n:] == 0x5A).all())
+
+
+# Columns 4 past a multiple of 8: bf16 rows start at 8 bytes and are stored 8
+# bytes at a time.  128 x 128 tiles (at most one per CU, and more), 256 x 128,
+# 256 x 256; a last column tile of 4 columns, and of all but 4.
+@pytest.mark.parametrize("M,N,K", [(129, 132, 96), (130, 252, 512), (2100, 2180, 512),
+                                   (300, 12300, 1024), (2900, 2820, 64), (2900, 2812, 608)])
+@pytest.mark.parametrize("residual", [True, False])
+def test_bf16_rows_of_4_past_a_multiple_of_8(M, N, K, residual):
+    q, w = _mx(M, N, K)
+    q = q if residual else (q[0], q[1], None, None)
+    print("bf16 rows at 8 bytes: M=%d N=%d K=%d" % (M, N, K), flush=True)
+    z, intact = _guarded(M, N, torch.bfloat16)
+    rfq.rfq_gemm(*q, *w, out=z)
+    # The same sums in fp32, rounded by torch.
+    assert torch.equal(z, rfq.rfq_gemm(*q, *w).bfloat16())
+    assert intact()
