@@ -886,7 +886,16 @@ bool use_mid_tiles(int64_t M, int64_t N) {
 // epilogue 38.9 -> 35.9, 512 rows x 12288 x 4096 37.2 -> 34.9 (plain 24.5 ->
 // 21.7), 700 x 8192 x 4096 36.4 -> 34.2, 1000 x 5000 x 2912 (320 and 160) 29.8
 // -> 29.6.  One stage in registers: 37.6 with the epilogue, the same without.
-bool use_tall_tiles(int64_t M, int64_t N) {
+// At short K the start of the loop and the epilogue, which two workgroups on a
+// CU overlap, take most of the time: from K = 1024 only (Mid against tall, 315 x
+// 12544 x 512 plain 6.2 / 6.5 us, 370 x 15532 x 512 9.6 / 11.2; 828 x 5156 x 1024
+// 13.0 / 13.0, 967 x 5888 x 1024 with a map 12.4 / 12.1), and with the SwiGLU
+// epilogue, the longer one, from K = 2048 (432 rows x 13952 x 512 9.9 / 10.2,
+// 1400 x 3264 x 1024 12.1 / 12.6, 6703 x 576 x 1536 14.6 / 15.6; 200 x 24576 x 4096
+// above), plain 1536 (1047 x 5568 x 1024 8.3 / 8.8; 591 x 7360 x 1536 11.6 / 10.4).
+constexpr int64_t kTallMinK = 1024, kTallSwigluMinK = 2048, kTallSwigluPlainMinK = 1536;
+bool use_tall_tiles(int64_t M, int64_t N, int64_t K, int64_t min_k = kTallMinK) {
+  if (K < min_k) return false;
   const int64_t mid = mid_tiles(M, N);
   const int64_t tall = ((M + Tall::kBM - 1) / Tall::kBM) * ((N + Tall::kBN - 1) / Tall::kBN);
   return mid > 256 && mid < 2 * 256 && tall <= 256;
@@ -983,11 +992,11 @@ static int64_t big_tile_rows(int64_t M, int64_t N) {
   return rows > 0 ? rows : ntm;
 }
 
-// Calls go(tile, first row, rows) for the tile shapes that M x N takes, with or
+// Calls go(tile, first row, rows) for the tile shapes that M x N x K takes, with or
 // without a map.
 template <class Go>
-static hipError_t on_tiles(int64_t M, int64_t N, Go go) {
-  if (use_tall_tiles(M, N)) return go(Tall{}, 0, M);
+static hipError_t on_tiles(int64_t M, int64_t N, int64_t K, Go go) {
+  if (use_tall_tiles(M, N, K)) return go(Tall{}, 0, M);
   if (use_mid_tiles(M, N))
     return use_deep_tiles(mid_tiles(M, N)) ? go(MidDeep{}, 0, M) : go(Mid{}, 0, M);
   const int64_t big_rows = std::min<int64_t>(big_tile_rows(M, N) * Big::kBM, M);
@@ -1004,7 +1013,7 @@ hipError_t launch_gemm_large(const uint8_t *q_codes, const uint8_t *q_scales,
                              const uint8_t *w_codes, const uint8_t *w_scales,
                              int64_t M, int64_t N, int64_t K, void *z, bool z_bf16,
                              hipStream_t stream) {
-  return on_tiles(M, N, [&](auto tile, int64_t row0, int64_t rows) {
+  return on_tiles(M, N, K, [&](auto tile, int64_t row0, int64_t rows) {
     using C = decltype(tile);
     // Activation rows [row0, row0 + rows) and the same rows of Z.
     const uint8_t *qc = q_codes + row0 * (K / 2), *qs = q_scales + row0 * (K / 32);
@@ -1027,7 +1036,7 @@ hipError_t launch_gemm_large_phi(const uint8_t *q_codes, const uint8_t *q_scales
                                  const uint8_t *w_codes, const uint8_t *w_scales,
                                  const uint8_t *phi, int64_t M, int64_t N, int64_t K, void *z,
                                  bool z_bf16, hipStream_t stream) {
-  return on_tiles(M, N, [&](auto tile, int64_t row0, int64_t rows) {
+  return on_tiles(M, N, K, [&](auto tile, int64_t row0, int64_t rows) {
     using C = decltype(tile);
     // row0 is a multiple of 256: whole rows of the map.
     const int64_t co = row0 * (K / 2), so = row0 * (K / 32);
@@ -1067,7 +1076,7 @@ hipError_t launch_gemm_swiglu(const uint8_t *q_codes, const uint8_t *q_scales,
                                                wgu_scales, M, N, K, nullptr, stream, so);
   };
   if (!use_mid_tiles(M, N)) return go(Big{});
-  if (use_tall_tiles(M, N)) return go(Tall{});
+  if (use_tall_tiles(M, N, K, r_codes ? kTallSwigluMinK : kTallSwigluPlainMinK)) return go(Tall{});
   return use_deep_tiles(mid_tiles(M, N)) ? go(MidDeep{}) : go(Mid{});
 }
 

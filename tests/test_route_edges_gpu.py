@@ -1,9 +1,11 @@
 """Where a product's store width or kernel changes with its sizes: the results on
 both sides of the line."""
+import numpy as np
 import pytest
 import torch
 
 import paper_2608_26581_amd as rfq
+from gpu_util import assert_gemm_close, host
 
 pytestmark = pytest.mark.gpu
 
@@ -40,3 +42,31 @@ def test_bf16_rows_of_4_past_a_multiple_of_8(M, N, K, residual):
     # The same sums in fp32, rounded by torch.
     assert torch.equal(z, rfq.rfq_gemm(*q, *w).bfloat16())
     assert intact()
+
+
+# 256 x 128 tiles from K = 1024 (SwiGLU epilogue: 2048, plain 1536), 128 x 128 below.
+@pytest.mark.parametrize("M,N,K", [(300, 12300, 992), (300, 12300, 1024), (520, 7200, 512)])
+def test_tall_tiles_from_their_shortest_k(orc, M, N, K):
+    q, w = _mx(M, N, K)
+    print("tall tiles: M=%d N=%d K=%d" % (M, N, K), flush=True)
+    z = host(rfq.rfq_gemm(*q, *w))
+    rows = np.unique(np.r_[0:4, 255:258, M - 3:M, 130:M:29])
+    zr, bound = orc.gemm(*[host(t)[rows] for t in q], host(w[0]), host(w[1]))
+    assert_gemm_close(z[rows], zr, bound, False, "product")
+    ones = torch.ones(((M + 63) // 64, (K + 255) // 256), dtype=torch.uint8, device="cuda")
+    assert np.array_equal(host(rfq.rfq_gemm_phi(*q, *w, ones)), z)
+
+
+@pytest.mark.parametrize("K,residual", [(1536, True), (2048, True), (1024, False), (1536, False)])
+def test_tall_swiglu_tiles_from_their_shortest_k(K, residual):
+    """The same codes as the chain of product and SwiGLU quantizer."""
+    M, Nh = 300, 6144
+    q, w = _mx(M, 2 * Nh, K)
+    q = q if residual else (q[0], q[1], None, None)
+    print("tall SwiGLU tiles: K=%d" % K, flush=True)
+    got = rfq.rfq_gemm_swiglu_quantize(*q, *w)
+    gu = rfq.rfq_gemm(*q, *w, out_dtype=torch.bfloat16).view(M, Nh // 32, 2, 32)
+    g, u = (gu[:, :, i].reshape(M, Nh).contiguous() for i in (0, 1))
+    want = rfq.rfq_swiglu_quantize_act(g, u)
+    for a, b in zip(got[:4], want[:4]):
+        assert torch.equal(a, b)
