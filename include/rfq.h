@@ -133,9 +133,13 @@ rfq_status rfq_gemm(const uint8_t *q_codes, const uint8_t *q_scales,
  * K >= 8192 where the few-row product's grid holds between one and two
  * workgroups per CU, e.g. N = 5120), e.g. an MLP down projection for a few
  * dozen to a few hundred tokens; not for 33-64 rows with 11264 <= N < 16384,
- * where rfq_gemm's few-row product is faster, and not, from N = 512, where K
- * is too short (with N <= 4096 K <= 3072, or K <= 4096 outside 65-192 rows; with
- * wider N K <= 2048 outside 65-128 rows).  Where the few-row grid's last
+ * where rfq_gemm's few-row product is faster, and not where K is too short:
+ * up to 1024; up to 128 rows, from N = 512, up to 3072 (N <= 4096; up to 4096
+ * with up to 64 rows) or below 2048 (wider N; up to 2048 with up to 64 rows);
+ * with more rows and K <= 4096 where the partial sums cost more than the
+ * columns saved, K - K / parts (at least 1550 columns, 900 a million partial
+ * sums beyond the first 860000; for a plain product about 1.7 times that: it
+ * may run unsplit where the RFQ product splits).  Where the few-row grid's last
  * round of workgroups is at most a quarter full (e.g. N = 5120) with up to
  * 16 rows and K >= 12288, the few-row product itself splits K in three
  * parts.
@@ -181,8 +185,8 @@ rfq_status rfq_gemm_split_noalloc(const uint8_t *q_codes, const uint8_t *q_scale
  * Workspace rfq_gemm_split uses for this shape: parts * M * N * 4 bytes for
  * the fp32 partials (at most 32 MiB), or 0 where it does not split (up to
  * 32 rows, 23 with K >= 12288, except the uneven few-row grids above;
- * 33-64 rows with 11264 <= N < 16384, K too short as above or at most 512,
- * more than 128 tiles of 128 x 128 with K < 8192 or more than 192, or sizes
+ * 33-64 rows with 11264 <= N < 16384, K too short as above (taken with the
+ * residual), more than 128 tiles of 128 x 128 with K < 8192 or more than 192, or sizes
  * that rfq_gemm rejects).  Assumes 16-byte aligned scale tensors (with others the
  * product runs unsplit).  Host-only; no device call.
  */

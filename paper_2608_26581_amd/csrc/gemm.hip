@@ -32,6 +32,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -345,20 +346,36 @@ static bool few_rows_beat_split(int64_t M, int64_t N, int64_t K) {
   return M < min_rows;
 }
 
-// Where a split does not pay: each part is too short against the partial
-// sums' pass (a launch of its own, 3 to 5 us).  Measured unsplit / split, bf16
-// Z, 40 to 512 rows: K = 1024 3.8 / 7.6 (40 x 1024) to 7.1 / 20.1 (512 x 4096),
-// K = 2048 5.4 / 8.1 (40 x 1024) to 10.6 / 21.9 (512 x 4096), K = 3072 7.7 /
-// 10.9 (40 x 4096) to 14.2 / 22.9 (512 x 4096), K = 4096 10.2 / 12.2 (40 x
-// 4096), 17.3 / 21.6 (256 x 4096).  At K = 4096 and 65-192 rows it depends on N
-// (19.6 / 15.1 at 100 x 3072, 14.0 / 17.4 at 100 x 4096), and 65-128 rows at
-// N = 8192 gain from K = 2048 on (12.0 / 11.4): split there as at longer K.
-// Narrow outputs (below N = 512) have too few workgroups unsplit (160 x 300
-// x 2560: 12.9 / 10.4).
-static bool too_short_to_split(int64_t M, int64_t N, int64_t K) {
-  if (N < 512 || K > 4096) return false;
-  if (N <= 4096) return K <= 3072 || M <= 64 || M > 192;
-  return K <= 2048 && (M <= 64 || M > 128);
+// Where a split does not pay against the partial sums' pass (a launch of its
+// own, 3 to 5 us, and the sums' traffic).  Unsplit / split, bf16 Z, us: nowhere
+// up to K = 1024 (40 x 1024 x 1024 3.8 / 7.6, 502 x 102 x 1024 8.0 / 9.5).
+//
+// Up to 128 rows, where the few-row kernel is the alternative, from N = 512 not up
+// to K = 3072, nor with up to 64 rows to 4096 (40 x 4096 x 3072 7.7 / 10.9, x 4096
+// 10.2 / 12.2; at K = 4096 and 65-128 rows it depends on N: 100 x 3072 19.6 / 15.1,
+// 100 x 4096 14.0 / 17.4); N above 4096 gains from K = 2048 with 65 rows or more
+// (100 x 8192 x 2048 12.0 / 11.4; 76 x 6539 x 1536 8.3 / 12.3).
+//
+// Above 128 rows, up to K = 4096: with p parts the product saves K (1 - 1/p) of
+// its K, about 3 ns a column with the residual and 2 without, and pays 2.4 us a
+// million partial sums and at least 4.7 us.  213 x 512 x 3584 (8 tiles of 128 x
+// 128) 14.5 / 10.6, 256 x 1024 x 4096 16.2 / 13.5, 143 x 996 x 2208 11.8 / 10.9;
+// 521 x 192 x 2048 9.7 / 10.2, 256 x 1344 x 3072 12.7 / 13.8, 512 x 4096 x 2048
+// 10.6 / 21.9; plain 342 x 64 x 4480 13.7 / 10.7, 189 x 196 x 3584 10.7 / 10.1,
+// 216 x 708 x 2560 8.7 / 10.0, 279 x 576 x 3584 10.6 / 11.6.
+static bool too_short_to_split(int64_t M, int64_t N, int64_t K, bool residual) {
+  if (K > 4096) return false;
+  if (K <= 1024) return true;
+  if (M <= 128) {
+    if (N < 512) return false;
+    if (N <= 4096) return K <= 3072 || M <= 64;
+    return K < 2048 || (K == 2048 && M <= 64);
+  }
+  const int64_t parts = splitk_plan(M, N, K).parts;
+  if (parts < 2) return true;
+  const int64_t saved = K - K / parts, sums = parts * M * N;
+  return residual ? saved <= std::max<int64_t>(1550, 775 + sums * 9 / 10000)
+                  : saved <= std::max<int64_t>(2300, 1240 + sums * 17 / 10000);
 }
 
 int64_t gemm_split_bytes(int64_t M, int64_t N, int64_t K) {
@@ -367,7 +384,8 @@ int64_t gemm_split_bytes(int64_t M, int64_t N, int64_t K) {
     const int parts = skinny_split_parts(M, N, K);
     return parts > 1 ? int64_t(parts) * M * N * 4 : 0;
   }
-  if (too_short_to_split(M, N, K)) return 0;
+  // (A plain product may leave the workspace unused where this one splits.)
+  if (too_short_to_split(M, N, K, true)) return 0;
   const SplitPlan p = splitk_plan(M, N, K);
   return p.parts > 1 ? p.work_bytes : 0;
 }
@@ -379,7 +397,7 @@ hipError_t launch_gemm(const uint8_t *q_codes, const uint8_t *q_scales,
                        hipStream_t stream, float *work, int64_t work_bytes) {
   const bool large = gemm_large_applies(q_scales, r_scales, w_scales, M, N, K);
   SplitPlan plan{1, K, 0};
-  if (large && work && !too_short_to_split(M, N, K)) {
+  if (large && work && !too_short_to_split(M, N, K, r_codes != nullptr)) {
     plan = splitk_plan(M, N, K);
     if (plan.work_bytes > work_bytes) plan = SplitPlan{1, K, 0};
   }

@@ -350,8 +350,27 @@ def test_gemm_split_validation_and_workspace_sizes():
     assert w(64, 12288, 4096) == 0                         # few-row kernel, 64 weight rows
     assert w(48, 13824, 5120) == 0                         # the same
     assert w(64, 16384, 12288) == 2 * 64 * 16384 * 4       # 128 tiles, from N = 16384: split
-    assert w(129, 4096, 12300) == 0                        # K not a multiple of 512
+    assert w(129, 4096, 12300) == 0                        # K not a multiple of 32
     assert w(-1, 4096, 12288) == 0 and w(129, 4096, 100) == 0
+
+
+def test_gemm_split_at_short_k():
+    """Above 128 rows and up to K = 4096 the columns that the parts save are set
+    against the partial sums; nothing splits up to K = 1024."""
+    w = _lib().rfq_gemm_workspace_bytes
+    assert w(256, 512, 4096) == 8 * 256 * 512 * 4          # 8 tiles: 3584 columns, 1.0 M sums
+    assert w(256, 1024, 4096) == 8 * 256 * 1024 * 4        # 16 tiles
+    assert w(213, 512, 3584) == 7 * 213 * 512 * 4
+    assert w(278, 512, 2560) == 5 * 278 * 512 * 4
+    assert w(150, 200, 2848) == 6 * 150 * 200 * 4          # ragged K
+    assert w(256, 1344, 3072) == 0                         # 2.1 M sums for 2560 columns
+    assert w(256, 4096, 4096) == 0                         # 64 tiles: 4.2 M sums
+    assert w(521, 192, 2048) == 0                          # 1536 columns
+    assert w(502, 102, 1024) == 0 and w(1405, 320, 576) == 0
+    assert w(99, 13632, 1216) == 0                         # 65-128 rows, wide N: from K = 2048
+    assert w(100, 8192, 2048) == 4 * 100 * 8192 * 4
+    assert w(60, 1024, 4096) == 0 and w(40, 300, 1024) == 0
+    assert w(40, 96, 1056) == 3 * 40 * 96 * 4
 
 
 def test_hif4_gemm_split_validation_and_workspace_sizes():

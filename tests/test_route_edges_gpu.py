@@ -70,3 +70,21 @@ def test_tall_swiglu_tiles_from_their_shortest_k(K, residual):
     want = rfq.rfq_swiglu_quantize_act(g, u)
     for a, b in zip(got[:4], want[:4]):
         assert torch.equal(a, b)
+
+
+# Splits above 128 rows at short K: parts of 512 and of 1024 columns, the
+# residual split and the plain product not, and ragged K.
+@pytest.mark.parametrize("M,N,K", [(213, 512, 3584), (256, 576, 4096), (150, 200, 2848),
+                                   (1130, 200, 4096), (256, 1344, 3072)])
+@pytest.mark.parametrize("residual", [True, False])
+def test_split_at_short_k(orc, M, N, K, residual):
+    q, w = _mx(M, N, K)
+    q = q if residual else (q[0], q[1], None, None)
+    print("split at short K: M=%d N=%d K=%d" % (M, N, K), flush=True)
+    z, intact = _guarded(M, N, torch.float32)
+    rfq.rfq_gemm(*q, *w, out=z, split=True)
+    rows = np.unique(np.r_[0:4, M - 3:M, 0:M:17])
+    zr, bound = orc.gemm(*[None if t is None else host(t)[rows] for t in q], host(w[0]),
+                         host(w[1]))
+    assert_gemm_close(host(z)[rows], zr, bound, False, "split")
+    assert intact()
