@@ -289,8 +289,13 @@ constexpr int kFM = kTM / 32;
 
 // BN = 256 weight rows per tile, or 128 where 256-row tiles would leave CUs
 // idle (fewer activation rows).
-template <bool RES, int BN, bool WBF16>
+//
+// PAIR (BN = 128 without the residual): four producer waves and two buffers of
+// 32 KB, so that two workgroups fit a CU; for grids of more than one 128-wide
+// tile per CU, which otherwise run in two rounds (see plain_pair).
+template <bool RES, int BN, bool WBF16, bool PAIR = false>
 struct HSmem {
+  static_assert(!PAIR || (!RES && BN == 128), "two workgroups fit a CU");
   static constexpr int kWRow0 = (RES ? 2 : 1) * kBM;    // q rows, r rows, then w rows
   static constexpr int kRows = kWRow0 + BN;
   static constexpr int kBufBytes = kRows * kRowBytes;
@@ -298,14 +303,14 @@ struct HSmem {
   // step's first fragments before the barrier that ends the step before it;
   // bf16 weights gain nothing from it, and two buffers of BN = 256 fill the
   // LDS).
-  static constexpr int kBufs = BN == 128 && !WBF16 ? 3 : 2;
+  static constexpr int kBufs = BN == 128 && !WBF16 && !PAIR ? 3 : 2;
   static constexpr int kBytes = kBufs * kBufBytes;
   // Producer waves: each lane decodes two half-block rows per step (8 waves,
   // two per SIMD, with the residual and BN = 256), with BN = 128 one (12 waves,
   // three per SIMD, where 6 left two SIMDs with twice the decode of the others:
   // 512 rows x 12288 x 4096 170.9 -> 163.8 us, plain 300 x 5120 x 13824 199.3
   // -> 161.1).
-  static constexpr int kProducers = kRows / (BN == 128 ? 32 : 64);
+  static constexpr int kProducers = kRows / (BN == 128 && !PAIR ? 32 : 64);
   static constexpr int kThreads = (kProducers + 4) * 64;
   static constexpr int kTN = BN / 2, kFN = kTN / 32;
 };
@@ -430,15 +435,15 @@ __device__ __forceinline__ void store_tile(const v16f (&acc)[kFM][FN], int64_t m
 // SPLIT: the grid holds ceil(K / ksplit) copies of the tile grid, copy s
 // multiplying K columns [s ksplit, (s + 1) ksplit) (ksplit a multiple of 64)
 // and writing its fp32 partial product to z + s M N.
-template <bool RES, bool ZBF16, bool WBF16, int BN, bool SPLIT = false>
-__global__ __launch_bounds__((HSmem<RES, BN, WBF16>::kThreads)) void hif4_gemm_kernel(
+template <bool RES, bool ZBF16, bool WBF16, int BN, bool SPLIT = false, bool PAIR = false>
+__global__ __launch_bounds__((HSmem<RES, BN, WBF16, PAIR>::kThreads)) void hif4_gemm_kernel(
     const uint8_t *__restrict__ qc, const uint32_t *__restrict__ qm,
     const uint8_t *__restrict__ rc, const uint32_t *__restrict__ rm,
     const uint8_t *__restrict__ wc, const uint32_t *__restrict__ wm,
     const uint16_t *__restrict__ wv, int64_t M, int64_t N, int64_t K, void *__restrict__ z,
     int64_t ksplit) {
   static_assert(!SPLIT || !ZBF16, "split partials are fp32");
-  using S = HSmem<RES, BN, WBF16>;
+  using S = HSmem<RES, BN, WBF16, PAIR>;
   constexpr int kTN = S::kTN, kFN = S::kFN;
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
 
@@ -500,43 +505,55 @@ __global__ __launch_bounds__((HSmem<RES, BN, WBF16>::kThreads)) void hif4_gemm_k
     // 189.5 us against 163.7; two or four steps ahead: no more).  Whether an
     // item is a weight row is uniform over a wave.
     constexpr int kV = WBF16 ? 4 : 1;
-    u32x4 cw[kItems][kV];
-    uint32_t mw[kItems];
-    auto load = [&](int s) {
+    struct Items {
+      u32x4 c[kItems][kV];
+      uint32_t m[kItems];
+    };
+    Items cur, next;
+    auto load = [&](int s, Items &t) {
 #pragma unroll
       for (int i = 0; i < kItems; ++i) {
         if (WBF16 && is_w[i]) {
 #pragma unroll
-          for (int v = 0; v < kV; ++v) cw[i][v] = vsrc[i][(int64_t)s * 8 + v];
+          for (int v = 0; v < kV; ++v) t.c[i][v] = vsrc[i][(int64_t)s * 8 + v];
         } else {
-          cw[i][0] = *reinterpret_cast<const u32x4 *>(src[i] + (int64_t)s * 32);
-          mw[i] = msrc[i][s];
+          t.c[i][0] = *reinterpret_cast<const u32x4 *>(src[i] + (int64_t)s * 32);
+          t.m[i] = msrc[i][s];
         }
       }
     };
+    // The short reductions that PAIR runs on codes gain from a second set, loaded
+    // before step s is decoded and taken over after the barrier that hands it on
+    // (937 rows x 5184 x 192: 11.0 us in place, 10.0).
+    constexpr bool kAhead = PAIR && !WBF16;
     auto produce = [&](int s, int b) {
+      if constexpr (kAhead) {
+        if (s + 1 < nsteps) load(s + 1, next);
+        __builtin_amdgcn_sched_barrier(0);   // (else the loads sink below the decode)
+      }
       uint8_t *buf = smem + b * S::kBufBytes;
 #pragma unroll
       for (int i = 0; i < kItems; ++i) {
         if (WBF16 && is_w[i]) {
 #pragma unroll
           for (int q = 0; q < 4; ++q)
-            *reinterpret_cast<u32x4 *>(buf + hswz(lrow[i], 4 * h + q)) = cw[i][q % kV];
+            *reinterpret_cast<u32x4 *>(buf + hswz(lrow[i], 4 * h + q)) = cur.c[i][q % kV];
         } else {
-          const uint32_t d[4] = {cw[i][0].x, cw[i][0].y, cw[i][0].z, cw[i][0].w};
-          const HalfUnits u = half_units(mw[i], h);
+          const uint32_t d[4] = {cur.c[i][0].x, cur.c[i][0].y, cur.c[i][0].z, cur.c[i][0].w};
+          const HalfUnits u = half_units(cur.m[i], h);
 #pragma unroll
           for (int q = 0; q < 4; ++q)
             *reinterpret_cast<u32x4 *>(buf + hswz(lrow[i], 4 * h + q)) = decode8_bf16(d[q], u, q);
         }
       }
-      load(min(s + 1, nsteps - 1));
+      if constexpr (!kAhead) load(min(s + 1, nsteps - 1), cur);
     };
-    load(0);
+    load(0, cur);
     if constexpr (S::kBufs == 2) {
       for (int s = 0; s < nsteps; ++s) {
         produce(s, s & 1);
         __syncthreads();
+        if constexpr (kAhead) cur = next;
       }
     } else {
       produce(0, 0);
@@ -1266,13 +1283,13 @@ __global__ __launch_bounds__(WAVES * 64) void hif4_gemm_few_kernel(
   }
 }
 
-template <bool RES, bool ZBF16, bool WBF16, int BN, bool SPLIT = false>
+template <bool RES, bool ZBF16, bool WBF16, int BN, bool SPLIT = false, bool PAIR = false>
 hipError_t launch_tiles(const uint8_t *qc, const uint32_t *qm, const uint8_t *rc,
                         const uint32_t *rm, const uint8_t *wc, const uint32_t *wm,
                         const uint16_t *wv, int64_t M, int64_t N, int64_t K, void *z,
                         hipStream_t stream, int parts = 1, int64_t ksplit = 0) {
-  using S = HSmem<RES, BN, WBF16>;
-  auto kern = hif4_gemm_kernel<RES, ZBF16, WBF16, BN, SPLIT>;
+  using S = HSmem<RES, BN, WBF16, PAIR>;
+  auto kern = hif4_gemm_kernel<RES, ZBF16, WBF16, BN, SPLIT, PAIR>;
   static std::atomic<bool> attr_done[kMaxDevices];
   const hipError_t e = set_lds_limit(attr_done, reinterpret_cast<const void *>(kern), S::kBytes);
   if (e != hipSuccess) return e;
@@ -1366,6 +1383,18 @@ int few_split_parts(int64_t M, int64_t N, int64_t K) {
   return best;
 }
 
+// Two workgroups per CU for the plain product on 128-wide tiles where those
+// number more than the CUs, one / two per CU, us: on codes below K = 1024 (2787
+// rows x 2308 x 64 11.2 / 9.0, 937 x 5184 x 192 13.1 / 10.0, 682 x 7424 x 512 19.7 /
+// 17.9, 1265 x 4288 x 896 27.6 / 25.5; 2096 x 3840 x 1024 30.3 / 31.1, 652 x 8768 x
+// 5568 147 / 157: there the step that reads a quarter ahead wins), on bf16 weights
+// at every K (1900 x 2560 x 192 11.3 / 10.4, 512 x 12288 x 4096 87.6 / 75.6, 475 x
+// 12492 x 7104 154.8 / 127.3).
+template <bool WBF16>
+bool plain_pair(int64_t M, int64_t N, int64_t K) {
+  return ((M + kBM - 1) / kBM) * ((N + 127) / 128) > kFillTiles && (WBF16 || K < 1024);
+}
+
 template <bool RES, bool ZBF16, bool WBF16>
 hipError_t launch_hg(const uint8_t *qc, const uint32_t *qm, const uint8_t *rc,
                      const uint32_t *rm, const uint8_t *wc, const uint32_t *wm,
@@ -1402,8 +1431,13 @@ hipError_t launch_hg(const uint8_t *qc, const uint32_t *qm, const uint8_t *rc,
 #undef RFQ_FEW_S
     return hipErrorInvalidValue;
   }
-  if (((M + kBM - 1) / kBM) * ((N + 255) / 256) < kFillTiles)
+  if (((M + kBM - 1) / kBM) * ((N + 255) / 256) < kFillTiles) {
+    if constexpr (!RES)
+      if (plain_pair<WBF16>(M, N, K))
+        return launch_tiles<RES, ZBF16, WBF16, 128, false, true>(qc, qm, rc, rm, wc, wm, wv, M, N,
+                                                                 K, z, stream);
     return launch_tiles<RES, ZBF16, WBF16, 128>(qc, qm, rc, rm, wc, wm, wv, M, N, K, z, stream);
+  }
   return launch_tiles<RES, ZBF16, WBF16, 256>(qc, qm, rc, rm, wc, wm, wv, M, N, K, z, stream);
 }
 

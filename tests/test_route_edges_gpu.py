@@ -88,3 +88,31 @@ def test_split_at_short_k(orc, M, N, K, residual):
                          host(w[1]))
     assert_gemm_close(host(z)[rows], zr, bound, False, "split")
     assert intact()
+
+
+def _hif4(M, N, K):
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    x = torch.randn((M, K), generator=gen, device="cuda")
+    x[:, ::37] *= 40
+    w = torch.randn((N, K), generator=gen, device="cuda") * 0.02
+    return rfq.rfq_hif4_quantize(x), rfq.rfq_hif4_quantize(w, residual=False)[:2]
+
+
+# 128-wide tiles: 258, 260 and 510 of them (two workgroups of the plain product
+# per CU on codes below K = 1024, on bf16 weights at every K), and 256 (one).
+@pytest.mark.parametrize("M,N,K", [(300, 10950, 64), (1290, 3260, 128), (1921, 4301, 192),
+                                   (1290, 3260, 960), (1290, 3260, 1024), (1000, 4096, 128)])
+def test_hif4_plain_tiles_two_per_cu(M, N, K):
+    """The bits of the same rows in blocks of 150, whose tiles run one per CU."""
+    q, w = _hif4(M, N, K)
+    wv = rfq.rfq_hif4_dequant(*w, out_dtype=torch.bfloat16)
+    print("HiF4 plain tiles: M=%d N=%d K=%d" % (M, N, K), flush=True)
+    for dt in (torch.float32, torch.bfloat16):
+        z, intact = _guarded(M, N, dt)
+        rfq.rfq_hif4_gemm(q[0], q[1], None, None, *w, out=z)
+        want = torch.cat([rfq.rfq_hif4_gemm(q[0][r:r + 150], q[1][r:r + 150], None, None, *w,
+                                            out_dtype=dt) for r in range(0, M // 150 * 150, 150)])
+        assert torch.equal(z[:len(want)], want) and intact()
+        zb, intact = _guarded(M, N, dt)
+        rfq.rfq_hif4_gemm_wbf16(q[0], q[1], None, None, wv, out=zb)
+        assert torch.equal(zb, z) and intact()
