@@ -418,7 +418,9 @@ rfq_status rfq_hif4_gemm_wbf16(const uint8_t *q_codes, const uint32_t *q_meta,
  * 1024 rows, where K is not split, the workspace instead receives the
  * weights decoded to bf16 (N * K * 2 bytes, at most 1 GiB, in an order of the
  * library's own) and is multiplied from there: the bits of rfq_hif4_gemm,
- * without decoding W again for every 128 rows.
+ * without decoding W again for every 128 rows.  Where that is not faster (up to
+ * 256 tiles of 128 x 128; a plain product with K < 576 and fewer than 256 tiles
+ * of 128 x 256) the workspace stays unused.
  * Each part of K writes its fp32 partial
  * sums to the workspace; one pass then adds the parts in a fixed order and
  * rounds to z_dtype, so the result is deterministic but its fp32 summation

@@ -1611,13 +1611,29 @@ SplitPlan hif4_split_plan(int64_t M, int64_t N, int64_t K) {
   return p;
 }
 
+// Whether the workspace's decoded W pays against decoding it in the product
+// (rfq_hif4_gemm, the same bits), us, decoded / not.  Not while 128-wide tiles
+// number at most one per CU: the operand-order kernel has at most half as many
+// workgroups there (1024 rows x 4096 x 4096 93 / 83, plain 64 / 53; 2189 x 1792 x
+// 1472 42.4 / 32.7; 6073 x 96 x 64 plain 9.8 / 4.6).  Up to two per CU the plain
+// product gains from K = 576 (2517 x 2240 x 256 14.5 / 11.8, 1363 x 3264 x 512 19.0 /
+// 17.6, 1253 x 3424 x 768 22.8 / 23.3), with the residual at every K (4410 x 992 x
+// 128 12.2 / 12.9, 1347 x 3328 x 448 22.2 / 24.1), as both with more tiles (4368 x
+// 1920 x 512 plain 27.1 / 32.4).
+static bool decoded_w_pays(int64_t M, int64_t N, int64_t K, bool residual) {
+  const int64_t rows = (M + kBM - 1) / kBM;
+  if (rows * ((N + 127) / 128) <= kFillTiles) return false;
+  return residual || K >= 576 || rows * ((N + 255) / 256) >= kFillTiles;
+}
+
 hipError_t launch_hif4_gemm_split(const uint8_t *q_codes, const uint32_t *q_meta,
                                   const uint8_t *r_codes, const uint32_t *r_meta,
                                   const uint8_t *w_codes, const uint32_t *w_meta, int64_t M,
                                   int64_t N, int64_t K, void *z, bool z_bf16, float *work,
                                   int64_t work_bytes, hipStream_t stream) {
   const SplitPlan p = hif4_split_plan(M, N, K);
-  if (p.decode_w && work != nullptr && work_bytes >= p.work_bytes) {
+  if (p.decode_w && work != nullptr && work_bytes >= p.work_bytes &&
+      decoded_w_pays(M, N, K, r_codes != nullptr)) {
     uint16_t *wv = reinterpret_cast<uint16_t *>(work);
     if (N % 32 == 0)
       return launch_ordered(q_codes, q_meta, r_codes, r_meta, w_codes, w_meta, wv, M, N, K, z,

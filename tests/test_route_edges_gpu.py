@@ -116,3 +116,27 @@ def test_hif4_plain_tiles_two_per_cu(M, N, K):
         zb, intact = _guarded(M, N, dt)
         rfq.rfq_hif4_gemm_wbf16(q[0], q[1], None, None, wv, out=zb)
         assert torch.equal(zb, z) and intact()
+
+
+# Both sides of where W is decoded into the workspace: 256 tiles of 128 x 128 (not)
+# and 257 or more; the plain product with K = 512 (not) and 576 below 256 tiles of
+# 128 x 256; N not a multiple of 32 (row by row).
+@pytest.mark.parametrize("M,N,K", [(1024, 4096, 192), (1025, 4064, 192), (1300, 4224, 512),
+                                   (1300, 4224, 576), (1025, 4100, 512), (1025, 4100, 576),
+                                   (4100, 4096, 192)])
+@pytest.mark.parametrize("residual", [True, False])
+def test_hif4_decoded_weights_from_their_smallest_sizes(M, N, K, residual):
+    q, w = _hif4(M, N, K)
+    q = q if residual else (q[0], q[1], None, None)
+    nbytes = rfq.rfq_hif4_gemm_workspace_bytes(M, N, K)
+    assert nbytes == N * K * 2
+    print("HiF4 decoded weights: M=%d N=%d K=%d" % (M, N, K), flush=True)
+    ws = torch.full((nbytes + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    z, intact = _guarded(M, N, torch.float32)
+    rfq.rfq_hif4_gemm_split(*q, *w, ws[:nbytes], out=z)
+    assert torch.equal(z, rfq.rfq_hif4_gemm(*q, *w)) and intact()
+    assert (ws[nbytes:] == 0x5A).all()
+    # The line lies where the comments say: the workspace is written or not.
+    tiles, wide = -(-M // 128) * -(-N // 128), -(-M // 128) * -(-N // 256)
+    used = tiles > 256 and (residual or K >= 576 or wide >= 256)
+    assert bool((ws[:nbytes] != 0x5A).any()) == used
