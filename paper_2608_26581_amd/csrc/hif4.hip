@@ -77,14 +77,21 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 constexpr int kH = 64;                 // elements per HiF4 block
 constexpr int kQThreads = 256;
-// A lane takes one 8-element unit: the kernel is bound by instruction issue,
-// so as many waves as there are hide each other best.  Measured (bf16 input with
-// the residual, one unit / four units per lane): 64 rows x 4096 2.7 / 5.5 us, 300
-// x 13824 6.9 / 8.3, 2000 x 4096 11.0 / 12.8, 4096 x 4096 19.4 / 21.0, 8192 x 4096
-// 34.1 / 35.5; fp32 weights 12288 x 4096 40.9 / 43.6; two units lie between.  Four
-// from where a lane per unit would pass a launch's 2^32 work items.
+// 8-element units per lane, one or four, bf16 input unless said otherwise, us.
+// One: the kernel is bound by instruction issue, and as many waves as there are
+// hide each other best (with the residual 64 rows x 4096 2.7 / 5.5, 300 x 13824 6.0 /
+// 7.4, 4096 x 4096 18.9 / 19.7, 8192 x 4096 33.5 / 35.0; fp32 without it, the form
+// that reads most a unit, at every size: 12288 x 4096 41.1 / 43.5, 2^30 elements 875 /
+// 931; two units lie between).  Four: on tensors that take long enough, a workgroup
+// a kilobyte costs more to dispatch than the waves gain: bf16 without the residual
+// from 2^25 elements (8192 x 4096 20.05 / 20.0, 12288 x 4096 28.7 / 27.7, 2^27
+// elements 71.4 / 65.9), with the residual from 2^27 (119.2 / 118.4, 2^28 234.6 /
+// 230.3, fp32 267.0 / 263.9; at 2^26 bf16 61.9 / 62.7).
 constexpr int kQSteps = 4;
-constexpr int64_t kQSmallUnits = (int64_t(1) << 32) - kQThreads;
+constexpr int64_t kQFourUnits = int64_t(1) << 22, kQFourUnitsRes = int64_t(1) << 24;
+// Units a launch takes (its work items fit 32 bits, also at one unit a lane); a
+// larger tensor takes several launches.
+constexpr int64_t kQLaunchUnits = int64_t(1) << 28;
 constexpr int kLoopGrid = 1 << 16;     // dequantization grid cap (loops over the rest)
 
 // Every lane of these permutations has a source, so the old value never
@@ -1484,25 +1491,13 @@ hipError_t launch_ordered(const uint8_t *qc, const uint32_t *qm, const uint8_t *
   return z_bf16 ? go(std::false_type{}, std::true_type{}) : go(std::false_type{}, std::false_type{});
 }
 
-template <int STEPS>
-hipError_t launch_hq(const void *x, bool bf16_in, int64_t nunits, uint8_t *qc, uint32_t *qm,
-                     uint8_t *rc, uint32_t *rm, hipStream_t stream) {
-  const int64_t per_wg = (kQThreads / 64) * 64 * STEPS;
-  const dim3 grid((unsigned)((nunits + per_wg - 1) / per_wg)), block(kQThreads);
-  if (bf16_in) {
-    if (rc)
-      hif4_quantize_kernel<true, true, STEPS><<<grid, block, 0, stream>>>(x, nunits, qc, qm, rc, rm);
-    else
-      hif4_quantize_kernel<true, false, STEPS><<<grid, block, 0, stream>>>(x, nunits, qc, qm,
-                                                                          nullptr, nullptr);
-  } else {
-    if (rc)
-      hif4_quantize_kernel<false, true, STEPS><<<grid, block, 0, stream>>>(x, nunits, qc, qm, rc,
-                                                                          rm);
-    else
-      hif4_quantize_kernel<false, false, STEPS><<<grid, block, 0, stream>>>(x, nunits, qc, qm,
-                                                                           nullptr, nullptr);
-  }
+template <bool BF16_IN, bool RES, int STEPS>
+hipError_t launch_hq(const void *x, int64_t nunits, uint8_t *qc, uint32_t *qm, uint8_t *rc,
+                     uint32_t *rm, hipStream_t stream) {
+  constexpr int64_t kPerWg = kQThreads * STEPS;
+  hif4_quantize_kernel<BF16_IN, RES, STEPS>
+      <<<dim3((unsigned)((nunits + kPerWg - 1) / kPerWg)), dim3(kQThreads), 0, stream>>>(
+          x, nunits, qc, qm, rc, rm);
   return hipGetLastError();
 }
 
@@ -1512,9 +1507,25 @@ hipError_t launch_hif4_quantize(const void *x, bool bf16_in, int64_t nelem, uint
                                 uint32_t *q_meta, uint8_t *r_codes, uint32_t *r_meta,
                                 hipStream_t stream) {
   const int64_t nunits = nelem / 8;
-  if (nunits < kQSmallUnits)
-    return launch_hq<1>(x, bf16_in, nunits, q_codes, q_meta, r_codes, r_meta, stream);
-  return launch_hq<kQSteps>(x, bf16_in, nunits, q_codes, q_meta, r_codes, r_meta, stream);
+  const bool res = r_codes != nullptr;
+  const bool four = nunits >= (res ? kQFourUnitsRes : kQFourUnits);
+  for (int64_t u = 0; u < nunits; u += kQLaunchUnits) {
+    // From unit u (a whole block): 8 elements, 4 code bytes, an eighth of a word.
+    const void *xu = static_cast<const uint8_t *>(x) + u * (bf16_in ? 16 : 32);
+    uint8_t *qc = q_codes + 4 * u, *rc = res ? r_codes + 4 * u : nullptr;
+    uint32_t *qm = q_meta + u / 8, *rm = res ? r_meta + u / 8 : nullptr;
+    const int64_t n = std::min(kQLaunchUnits, nunits - u);
+    const hipError_t e =
+        bf16_in ? (res ? (four ? launch_hq<true, true, kQSteps>(xu, n, qc, qm, rc, rm, stream)
+                               : launch_hq<true, true, 1>(xu, n, qc, qm, rc, rm, stream))
+                       : (four ? launch_hq<true, false, kQSteps>(xu, n, qc, qm, rc, rm, stream)
+                               : launch_hq<true, false, 1>(xu, n, qc, qm, rc, rm, stream)))
+        : res   ? (four ? launch_hq<false, true, kQSteps>(xu, n, qc, qm, rc, rm, stream)
+                        : launch_hq<false, true, 1>(xu, n, qc, qm, rc, rm, stream))
+                : launch_hq<false, false, 1>(xu, n, qc, qm, rc, rm, stream);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_hif4_dequant(const uint8_t *codes, const uint32_t *meta, int64_t nelem,

@@ -140,3 +140,25 @@ def test_hif4_decoded_weights_from_their_smallest_sizes(M, N, K, residual):
     tiles, wide = -(-M // 128) * -(-N // 128), -(-M // 128) * -(-N // 256)
     used = tiles > 256 and (residual or K >= 576 or wide >= 256)
     assert bool((ws[:nbytes] != 0x5A).any()) == used
+
+
+# The HiF4 quantizer: four units a lane from 2^25 elements (with the residual 2^27;
+# fp32 without it one at every size), several launches past 2^31 elements.
+@pytest.mark.parametrize("M,dtype,residual", [
+    (8191, torch.bfloat16, False), (8193, torch.bfloat16, False), (8193, torch.float32, False),
+    (32769, torch.bfloat16, True), (32769, torch.float32, True),
+    ((1 << 19) + 3, torch.bfloat16, True), ((1 << 19) + 3, torch.float32, False)])
+def test_hif4_quantizer_units_and_launches(M, dtype, residual):
+    """The codes of blocks of 4096 rows, which a lane a unit quantizes in one
+    launch."""
+    K = 4096
+    print("HiF4 quantizer: M=%d %s residual=%s" % (M, dtype, residual), flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    x = torch.empty((M, K), dtype=dtype, device="cuda")
+    for r in range(0, M, 4096):
+        x[r:r + 4096] = torch.randn((min(4096, M - r), K), generator=gen, device="cuda")
+    q = rfq.rfq_hif4_quantize(x, residual=residual)
+    for r in range(0, M, 4096):
+        want = rfq.rfq_hif4_quantize(x[r:r + 4096], residual=residual)
+        for a, b in zip(q, want):
+            assert (a is None) == (b is None) and (a is None or torch.equal(a[r:r + 4096], b))
