@@ -154,7 +154,8 @@ def test_scale_byte_sweep_through_the_converters(orc, dtype):
     Eq. 3-4 and Sec. 4.3 Eq. 9-10 through the oracle (itself pinned against
     brute force on the same blocks), bit-exact; dequantization exact; the
     products of these codes within tolerance (byte 0 reaching the scaled
-    MFMA as 2^-127), on the general, few-row and large-tile kernels."""
+    MFMA as 2^-127), on the few-row kernel (a short group and a whole one)
+    and the large-tile kernel."""
     bf16 = dtype == torch.bfloat16
     x = scale_sweep_blocks(bf16)
     _say("scale byte sweep %s rows %d" % (dtype, x.shape[0]))
@@ -171,8 +172,8 @@ def test_scale_byte_sweep_through_the_converters(orc, dtype):
 
     row_bytes = np.array(list(SWEEP_SCALE_BYTES) + [0])
     rng = np.random.default_rng(31)
-    # K = 128: general kernel; 8 rows, K = 512: few-row kernel; 320 rows,
-    # K = 512: large-tile kernel.
+    # 8 rows, K = 128 (a short group) and 512: few-row kernel; 320 rows, K = 512:
+    # large-tile kernel.
     for reps, kreps in ((1, 1), (1, 4), (40, 4)):
         xs = np.tile(x, (reps, kreps))
         xst = torch.from_numpy(xs.astype(np.float32)).cuda().to(dtype)
@@ -685,8 +686,8 @@ PHI_SHAPES = [
     ("qwen", 200, 328, 1024),       # large-tile kernel, ragged M and N
     ("qwen", 129, 257, 2560),       # large-tile kernel, ragged indicator rows
     ("qwen", 512, 300, 2048),       # large-tile kernel, two full workgroup rows
-    ("qwen", 200, 328, 1056),       # general kernel, K not a multiple of 256
-    ("wan", 64, 96, 640),           # general kernel
+    ("qwen", 200, 328, 1056),       # large-tile kernel, K not a multiple of 256
+    ("wan", 64, 96, 640),           # few-row kernel, K not a multiple of 512
 ]
 
 
