@@ -59,10 +59,14 @@ bool product_fits(int64_t M, int64_t N) {
 }
 
 // HiF4 calls: K a positive multiple of 64 (one metadata word per 64-element
-// block).  The quantizer runs 256 work items per 128 blocks.  The product
-// runs one workgroup per 128 x 256 output tile (up to 768 work items: eight
-// producer waves with the residual, four consumers) or per 128 x 128 tile
-// (up to 640); both grids must fit, whichever the dispatch picks.
+// block).  The quantizer takes up to 2^31 - 128 blocks, in as many launches as
+// their work items need.  The product runs one workgroup per 128 x 256 output
+// tile (up to 768 work items: eight producer waves with the residual, four
+// consumers; 512 on decoded weights, also for 128 x 512 tiles), a grid that must
+// fit; 128-wide tiles (up to 1024 work items) are chosen only below 256 tiles of
+// 128 x 256, so at most 510 of them (times 8 parts of K) always fit.  Their 640
+// work items below are the limit that calls have always met at 128 to 256
+// columns, kept so that the same sizes are accepted.
 rfq_status check_k64(int64_t rows, int64_t K) {
   if (rows < 0 || K < 64 || (K % 64) != 0 || K > kMaxK) return RFQ_ERR_SHAPE;
   return RFQ_OK;
