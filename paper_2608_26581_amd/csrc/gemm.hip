@@ -358,11 +358,11 @@ static bool few_rows_beat_split(int64_t M, int64_t N, int64_t K) {
 //
 // Above 128 rows, up to K = 4096: with p parts the product saves K (1 - 1/p) of
 // its K, about 3 ns a column with the residual and 2 without, and pays 2.4 us a
-// million partial sums and at least 4.7 us.  213 x 512 x 3584 (8 tiles of 128 x
+// million partial sums and at least 4.4 us.  213 x 512 x 3584 (8 tiles of 128 x
 // 128) 14.5 / 10.6, 256 x 1024 x 4096 16.2 / 13.5, 143 x 996 x 2208 11.8 / 10.9;
-// 521 x 192 x 2048 9.7 / 10.2, 256 x 1344 x 3072 12.7 / 13.8, 512 x 4096 x 2048
-// 10.6 / 21.9; plain 342 x 64 x 4480 13.7 / 10.7, 189 x 196 x 3584 10.7 / 10.1,
-// 216 x 708 x 2560 8.7 / 10.0, 279 x 576 x 3584 10.6 / 11.6.
+// 182 x 512 x 2048 9.5 / 9.2; 207 x 1344 x 2048 9.6 / 10.7, 256 x 1344 x 3072 12.7 /
+// 13.8, 512 x 4096 x 2048 10.6 / 21.9; plain 342 x 64 x 4480 13.7 / 10.7, 446 x 71 x
+// 2720 11.0 / 9.7, 216 x 708 x 2560 8.7 / 10.0, 279 x 576 x 3584 10.6 / 11.6.
 static bool too_short_to_split(int64_t M, int64_t N, int64_t K, bool residual) {
   if (K > 4096) return false;
   if (K <= 1024) return true;
@@ -374,8 +374,8 @@ static bool too_short_to_split(int64_t M, int64_t N, int64_t K, bool residual) {
   const int64_t parts = splitk_plan(M, N, K).parts;
   if (parts < 2) return true;
   const int64_t saved = K - K / parts, sums = parts * M * N;
-  return residual ? saved <= std::max<int64_t>(1550, 775 + sums * 9 / 10000)
-                  : saved <= std::max<int64_t>(2300, 1240 + sums * 17 / 10000);
+  return residual ? saved <= std::max<int64_t>(1450, 775 + sums * 9 / 10000)
+                  : saved <= std::max<int64_t>(2200, 1240 + sums * 17 / 10000);
 }
 
 int64_t gemm_split_bytes(int64_t M, int64_t N, int64_t K) {
