@@ -137,8 +137,8 @@ rfq_status rfq_gemm(const uint8_t *q_codes, const uint8_t *q_scales,
  * up to 1024; up to 128 rows, from N = 512, up to 3072 (N <= 4096; up to 4096
  * with up to 64 rows) or below 2048 (wider N; up to 2048 with up to 64 rows);
  * with more rows and K <= 4096 where the partial sums cost more than the
- * columns saved, K - K / parts (at least 1550 columns, 900 a million partial
- * sums beyond the first 860000; for a plain product about 1.7 times that: it
+ * columns saved, K - K / parts (at least 1450 columns, 900 a million partial
+ * sums beyond the first 750000; for a plain product about 1.6 times that: it
  * may run unsplit where the RFQ product splits).  Where the few-row grid's last
  * round of workgroups is at most a quarter full (e.g. N = 5120) with up to
  * 16 rows and K >= 12288, the few-row product itself splits K in three
@@ -419,8 +419,8 @@ rfq_status rfq_hif4_gemm_wbf16(const uint8_t *q_codes, const uint32_t *q_meta,
  * weights decoded to bf16 (N * K * 2 bytes, at most 1 GiB, in an order of the
  * library's own) and is multiplied from there: the bits of rfq_hif4_gemm,
  * without decoding W again for every 128 rows.  Where that is not faster (up to
- * 256 tiles of 128 x 128; a plain product with K < 576 and fewer than 256 tiles
- * of 128 x 256) the workspace stays unused.
+ * 256 tiles of 128 x 128; a plain product with K < 576, 384 below N = 2048, and
+ * fewer than 256 tiles of 128 x 256) the workspace stays unused.
  * Each part of K writes its fp32 partial
  * sums to the workspace; one pass then adds the parts in a fixed order and
  * rounds to z_dtype, so the result is deterministic but its fp32 summation

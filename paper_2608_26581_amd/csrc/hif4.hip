@@ -1628,13 +1628,14 @@ SplitPlan hif4_split_plan(int64_t M, int64_t N, int64_t K) {
 // workgroups there (1024 rows x 4096 x 4096 93 / 83, plain 64 / 53; 2189 x 1792 x
 // 1472 42.4 / 32.7; 6073 x 96 x 64 plain 9.8 / 4.6).  Up to two per CU the plain
 // product gains from K = 576 (2517 x 2240 x 256 14.5 / 11.8, 1363 x 3264 x 512 19.0 /
-// 17.6, 1253 x 3424 x 768 22.8 / 23.3), with the residual at every K (4410 x 992 x
-// 128 12.2 / 12.9, 1347 x 3328 x 448 22.2 / 24.1), as both with more tiles (4368 x
-// 1920 x 512 plain 27.1 / 32.4).
+// 17.6, 1253 x 3424 x 768 22.8 / 23.3), below N = 2048, where W's decode is short,
+// from 384 (7316 x 608 x 192 12.1 / 10.1, 3607 x 1184 x 384 14.05 / 14.4, x 512 15.7 /
+// 16.8), with the residual at every K (4410 x 992 x 128 12.2 / 12.9, 1347 x 3328 x
+// 448 22.2 / 24.1), as both with more tiles (4368 x 1920 x 512 plain 27.1 / 32.4).
 static bool decoded_w_pays(int64_t M, int64_t N, int64_t K, bool residual) {
   const int64_t rows = (M + kBM - 1) / kBM;
   if (rows * ((N + 127) / 128) <= kFillTiles) return false;
-  return residual || K >= 576 || rows * ((N + 255) / 256) >= kFillTiles;
+  return residual || K >= (N < 2048 ? 384 : 576) || rows * ((N + 255) / 256) >= kFillTiles;
 }
 
 hipError_t launch_hif4_gemm_split(const uint8_t *q_codes, const uint32_t *q_meta,

@@ -119,11 +119,11 @@ def test_hif4_plain_tiles_two_per_cu(M, N, K):
 
 
 # Both sides of where W is decoded into the workspace: 256 tiles of 128 x 128 (not)
-# and 257 or more; the plain product with K = 512 (not) and 576 below 256 tiles of
-# 128 x 256; N not a multiple of 32 (row by row).
+# and 257 or more; the plain product with K = 512 (not) and 576, below N =
+# 2048 320 (not) and 384, up to 256 tiles of 128 x 256; N not a multiple of 32 (row by row).
 @pytest.mark.parametrize("M,N,K", [(1024, 4096, 192), (1025, 4064, 192), (1300, 4224, 512),
                                    (1300, 4224, 576), (1025, 4100, 512), (1025, 4100, 576),
-                                   (4100, 4096, 192)])
+                                   (4100, 4096, 192), (3600, 1184, 320), (3600, 1184, 384)])
 @pytest.mark.parametrize("residual", [True, False])
 def test_hif4_decoded_weights_from_their_smallest_sizes(M, N, K, residual):
     q, w = _hif4(M, N, K)
@@ -138,7 +138,7 @@ def test_hif4_decoded_weights_from_their_smallest_sizes(M, N, K, residual):
     assert (ws[nbytes:] == 0x5A).all()
     # The line lies where the comments say: the workspace is written or not.
     tiles, wide = -(-M // 128) * -(-N // 128), -(-M // 128) * -(-N // 256)
-    used = tiles > 256 and (residual or K >= 576 or wide >= 256)
+    used = tiles > 256 and (residual or K >= (384 if N < 2048 else 576) or wide >= 256)
     assert bool((ws[:nbytes] != 0x5A).any()) == used
 
 
