@@ -1454,10 +1454,12 @@ int64_t ordered_tiles(int64_t M, int64_t N, int64_t bn) {
 }
 
 // 512-wide tiles where their rounds of 256 workgroups take less time; one
-// takes 1.86 times a round of 256-wide ones (4096 rows x 12288 x 4096, 3 against
-// 6 rounds, W's decode included: 629 against 674 us; 1024 rows, 1 against 2:
-// 195 against 219; 2048 x 4096 x 12288, 1 and 1: 463 against 347; 4000 x 5120 x
-// 13824, 2 and 3: 1150 against 989).
+// takes 1.86 times a round of 256-wide ones by 4096 rows x 12288 x 4096 (3 against
+// 6 rounds, W's decode included: 629 against 674 us) and 1.75 by others without W's
+// decode (1024 rows, 1 against 2: 195 against 219; 4000 x 5120 x 13824, 2 and 3:
+// 1150 against 989).  The rounds are n = 2 w or 2 w - 1 to w: 512-wide wherever n =
+// 2 w at either factor, and with n = 2 w - 1 from w = 8 (5 at 1.75: the few per
+// cent between have not been measured).  2048 x 4096 x 12288, 1 and 1: 463 / 347.
 bool ordered_wide(int64_t M, int64_t N) {
   auto rounds = [&](int64_t bn) {
     return (ordered_tiles(M, N, bn) + kFillTiles - 1) / kFillTiles;
@@ -1600,8 +1602,9 @@ static bool split_on_tiles(int64_t M, int64_t N, int64_t K, const SplitPlan &til
 // into the workspace, in operand order (N a multiple of 32) or row by row for
 // the bf16-weight product (the same bits as the codes form, whose tile rows
 // each decode all of W again).  Measured, bf16 Z, decode included: 4096 rows x
-// 12288 x 4096 799 -> 617 us, row by row 747; when the line was drawn, row by
-// row: 1024 rows x 12288 x 4096 268 -> 249, at 512 rows no gain (220 / 228).
+// 12288 x 4096 799 -> 617 us, row by row 747.  The line dates from the row by row
+// form (1024 rows x 12288 x 4096 268 -> 249 us, at 512 rows no gain: 220 / 228);
+// the operand order, 195 there, has not been measured below it.
 constexpr int64_t kDecodeMinRows = 1024;
 constexpr int64_t kDecodeMaxBytes = int64_t(1) << 30;
 
