@@ -198,8 +198,13 @@ struct WPair { WGroup f[F]; uint32_t phi[2]; };
 // workgroup) by 256 columns (two k-steps): the residual MFMAs of k-steps whose
 // byte is 0 are skipped.  The kernel is bound by W's codes, so this takes the
 // time of the product without a map.
+//
+// Three waves per SIMD with one fragment, except where that leaves too few
+// registers: at ragged K with four slices and the residual (180) it spilled 15
+// and was slower (64 rows x 4096 x 2880 7.5 us against 6.7 with two, 128 x 4000
+// x 5600 24.9 against 21.8).
 template <bool RES, bool ZBF16, int S, int F, bool GK, bool PHI>
-__global__ __launch_bounds__(kSkThreads, F == 1 && !(PHI && GK && S == 4) ? 3 : (F <= 2 ? 2 : 1)) void
+__global__ __launch_bounds__(kSkThreads, F == 1 && !(RES && GK && S == 4) ? 3 : (F <= 2 ? 2 : 1)) void
 rfq_gemm_skinny_kernel(
     const uint8_t *__restrict__ qc, const uint8_t *__restrict__ qs,
     const uint8_t *__restrict__ rc, const uint8_t *__restrict__ rs,
