@@ -12,6 +12,7 @@ not passed in.
 import ctypes
 import importlib.util
 import os
+import threading
 import warnings
 
 import torch
@@ -54,6 +55,7 @@ _lib = None
 # arguments first and go on in Python where they return None.  False where the
 # module cannot be used: every call then goes through Python.
 _calls = None
+_load_lock = threading.Lock()
 
 
 class RfqError(RuntimeError):
@@ -68,8 +70,14 @@ class RfqError(RuntimeError):
 def load():
     """Loads librfq.so once; raises if it has not been built."""
     global _lib
-    if _lib is not None:
-        return _lib
+    if _lib is None:
+        with _load_lock:
+            if _lib is None:
+                _lib = _load()
+    return _lib
+
+
+def _load():
     if not os.path.exists(LIB_PATH):
         raise RuntimeError(
             "librfq.so is not built (expected at %s); run __graft_entry__.build()" % LIB_PATH)
@@ -109,7 +117,6 @@ def load():
     lib.rfq_status_str.restype = ctypes.c_char_p
     lib.rfq_abi_version.argtypes = []
     lib.rfq_abi_version.restype = I32
-    _lib = lib
     return lib
 
 
@@ -142,13 +149,13 @@ def _load_calls():
 
 
 def _bind_calls(lib):
-    """Loads the native calls once and points them at lib's entry points."""
+    """Loads the native calls once and points them at lib's entry points; other
+    threads see the module from then on."""
     global _calls
-    if _calls is None:
-        _calls = _load_calls()
-    if not _calls:
-        return
-    _calls.bind(*(ctypes.cast(getattr(lib, f), ctypes.c_void_p).value for f in _NATIVE_ENTRIES))
+    calls = _load_calls() if _calls is None else _calls
+    if calls:
+        calls.bind(*(ctypes.cast(getattr(lib, f), ctypes.c_void_p).value for f in _NATIVE_ENTRIES))
+    _calls = calls
 
 
 # dtype codes of out_dtype for the native calls (others: checked in Python).

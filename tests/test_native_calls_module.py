@@ -1,6 +1,8 @@
 """The native calls' module on the CPU: it loads with the installed torch, and
 without it (not built, no library, built against another torch, no compiler)
 librfq builds and the binding works, with a warning."""
+import threading
+import time
 import warnings
 
 import pytest
@@ -54,3 +56,35 @@ def test_build_without_a_host_compiler(monkeypatch, tmp_path):
     with pytest.warns(RuntimeWarning, match="not built"):
         assert rfq_build.build_calls_if_possible() is None
     assert not path.exists()
+
+
+def test_module_is_published_bound(monkeypatch):
+    """Another thread's first call may come at any point of the load: it must not
+    find the module before its entry points are set, nor load a second one."""
+    seen, modules = [], []
+
+    class Calls:
+        def bind(self, *entries):
+            seen.append(binding._calls)
+            assert len(entries) == len(binding._NATIVE_ENTRIES) and all(entries)
+
+        def hif4_quantize(self, x, residual):
+            return "served"
+
+    def load_calls():
+        modules.append(Calls())
+        time.sleep(0.05)
+        return modules[-1]
+
+    _fresh(monkeypatch)
+    monkeypatch.setattr(binding, "_load_calls", load_calls)
+    results = []
+    threads = [threading.Thread(target=lambda: results.append(binding._native(
+        "hif4_quantize", None, True))) for _ in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert results == ["served"] * 4
+    assert seen == [None] and len(modules) == 1
+    assert binding._calls is modules[0] and binding._lib is not None
