@@ -44,6 +44,22 @@ def test_bf16_rows_of_4_past_a_multiple_of_8(M, N, K, residual):
     assert intact()
 
 
+# fp32 rows of whole and of broken 16-byte chunks, on each tile shape.
+@pytest.mark.parametrize("M,N,K", [(129, 132, 96), (129, 131, 96), (130, 253, 512), (2100, 2180, 512),
+                                   (2100, 2179, 512), (300, 12300, 1024), (300, 12301, 2048),
+                                   (2900, 2820, 64), (2900, 2822, 608)])
+@pytest.mark.parametrize("residual", [True, False])
+def test_fp32_rows(M, N, K, residual):
+    q, w = _mx(M, N, K)
+    q = q if residual else (q[0], q[1], None, None)
+    print("fp32 rows: M=%d N=%d K=%d" % (M, N, K), flush=True)
+    z, intact = _guarded(M, N, torch.float32)
+    rfq.rfq_gemm(*q, *w, out=z)
+    # The same sums, which the bf16 store rounds.
+    assert torch.equal(z.bfloat16(), rfq.rfq_gemm(*q, *w, out_dtype=torch.bfloat16))
+    assert intact()
+
+
 # 256 x 128 tiles from K = 1024 (SwiGLU epilogue: 2048, plain 1536), 128 x 128 below.
 @pytest.mark.parametrize("M,N,K", [(300, 12300, 992), (300, 12300, 1024), (520, 7200, 512)])
 def test_tall_tiles_from_their_shortest_k(orc, M, N, K):
