@@ -925,7 +925,16 @@ bool use_mid_tiles(int64_t M, int64_t N) {
 // 1400 x 3264 x 1024 12.1 / 12.6, 6703 x 576 x 1536 14.6 / 15.6; 200 x 24576 x 4096
 // above), plain 1536 (1047 x 5568 x 1024 8.3 / 8.8; 591 x 7360 x 1536 11.6 / 10.4).
 constexpr int64_t kTallMinK = 1024, kTallSwigluMinK = 2048, kTallSwigluPlainMinK = 1536;
-bool use_tall_tiles(int64_t M, int64_t N, int64_t K, int64_t min_k = kTallMinK) {
+// Rows of Z that do not start at multiples of 16 bytes are stored in smaller
+// pieces, the longest epilogue of the product: from K = 2048 (bf16 272 rows x 11019 x
+// 1024 16.3 / 20.7, 4515 x 1365 x 1536 24.6 / 26.2, 302 x 10927 x 1536 plain 15.1 /
+// 19.3, fp32 20.2 / 23.0; bf16 566 x 6860 x 2048 plain 16.7 / 13.9, 664 x 7924 x 2048
+// 21.6 / 20.4, 888 x 6611 x 2048 29.7 / 30.2, 153 x 28884 x 2784 35.6 / 26.2).
+constexpr int64_t kTallBrokenRowsMinK = 2048;
+int64_t tall_min_k(int64_t N, bool z_bf16) {
+  return N % (z_bf16 ? 8 : 4) ? kTallBrokenRowsMinK : kTallMinK;
+}
+bool use_tall_tiles(int64_t M, int64_t N, int64_t K, int64_t min_k) {
   if (K < min_k) return false;
   const int64_t mid = mid_tiles(M, N);
   const int64_t tall = ((M + Tall::kBM - 1) / Tall::kBM) * ((N + Tall::kBN - 1) / Tall::kBN);
@@ -1026,8 +1035,8 @@ static int64_t big_tile_rows(int64_t M, int64_t N) {
 // Calls go(tile, first row, rows) for the tile shapes that M x N x K takes, with or
 // without a map.
 template <class Go>
-static hipError_t on_tiles(int64_t M, int64_t N, int64_t K, Go go) {
-  if (use_tall_tiles(M, N, K)) return go(Tall{}, 0, M);
+static hipError_t on_tiles(int64_t M, int64_t N, int64_t K, bool z_bf16, Go go) {
+  if (use_tall_tiles(M, N, K, tall_min_k(N, z_bf16))) return go(Tall{}, 0, M);
   if (use_mid_tiles(M, N))
     return use_deep_tiles(mid_tiles(M, N)) ? go(MidDeep{}, 0, M) : go(Mid{}, 0, M);
   const int64_t big_rows = std::min<int64_t>(big_tile_rows(M, N) * Big::kBM, M);
@@ -1044,7 +1053,7 @@ hipError_t launch_gemm_large(const uint8_t *q_codes, const uint8_t *q_scales,
                              const uint8_t *w_codes, const uint8_t *w_scales,
                              int64_t M, int64_t N, int64_t K, void *z, bool z_bf16,
                              hipStream_t stream) {
-  return on_tiles(M, N, K, [&](auto tile, int64_t row0, int64_t rows) {
+  return on_tiles(M, N, K, z_bf16, [&](auto tile, int64_t row0, int64_t rows) {
     using C = decltype(tile);
     // Activation rows [row0, row0 + rows) and the same rows of Z.
     const uint8_t *qc = q_codes + row0 * (K / 2), *qs = q_scales + row0 * (K / 32);
@@ -1067,7 +1076,7 @@ hipError_t launch_gemm_large_phi(const uint8_t *q_codes, const uint8_t *q_scales
                                  const uint8_t *w_codes, const uint8_t *w_scales,
                                  const uint8_t *phi, int64_t M, int64_t N, int64_t K, void *z,
                                  bool z_bf16, hipStream_t stream) {
-  return on_tiles(M, N, K, [&](auto tile, int64_t row0, int64_t rows) {
+  return on_tiles(M, N, K, z_bf16, [&](auto tile, int64_t row0, int64_t rows) {
     using C = decltype(tile);
     // row0 is a multiple of 256: whole rows of the map.
     const int64_t co = row0 * (K / 2), so = row0 * (K / 32);

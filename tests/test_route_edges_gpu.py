@@ -60,8 +60,10 @@ def test_fp32_rows(M, N, K, residual):
     assert intact()
 
 
-# 256 x 128 tiles from K = 1024 (SwiGLU epilogue: 2048, plain 1536), 128 x 128 below.
-@pytest.mark.parametrize("M,N,K", [(300, 12300, 992), (300, 12300, 1024), (520, 7200, 512)])
+# 256 x 128 tiles from K = 1024 (SwiGLU epilogue: 2048, plain 1536; rows of Z
+# that do not start at 16 bytes: 2048), 128 x 128 below.
+@pytest.mark.parametrize("M,N,K", [(300, 12300, 992), (300, 12300, 1024), (520, 7200, 512),
+                                   (300, 12301, 1024), (300, 12301, 2016), (300, 12301, 2048)])
 def test_tall_tiles_from_their_shortest_k(orc, M, N, K):
     q, w = _mx(M, N, K)
     print("tall tiles: M=%d N=%d K=%d" % (M, N, K), flush=True)
@@ -71,6 +73,10 @@ def test_tall_tiles_from_their_shortest_k(orc, M, N, K):
     assert_gemm_close(z[rows], zr, bound, False, "product")
     ones = torch.ones(((M + 63) // 64, (K + 255) // 256), dtype=torch.uint8, device="cuda")
     assert np.array_equal(host(rfq.rfq_gemm_phi(*q, *w, ones)), z)
+    zb, intact = _guarded(M, N, torch.bfloat16)
+    rfq.rfq_gemm(*q, *w, out=zb)
+    assert torch.equal(zb, torch.from_numpy(z).cuda().bfloat16()) and intact()
+    assert torch.equal(rfq.rfq_gemm_phi(*q, *w, ones, out_dtype=torch.bfloat16), zb)
 
 
 @pytest.mark.parametrize("K,residual", [(1536, True), (2048, True), (1024, False), (1536, False)])
