@@ -357,12 +357,13 @@ static bool few_rows_beat_split(int64_t M, int64_t N, int64_t K) {
 // (100 x 8192 x 2048 12.0 / 11.4; 76 x 6539 x 1536 8.3 / 12.3).
 //
 // Above 128 rows, up to K = 4096: with p parts the product saves K (1 - 1/p) of
-// its K, about 3 ns a column with the residual and 2 without, and pays 2.4 us a
-// million partial sums and at least 4.4 us.  213 x 512 x 3584 (8 tiles of 128 x
-// 128) 14.5 / 10.6, 256 x 1024 x 4096 16.2 / 13.5, 143 x 996 x 2208 11.8 / 10.9;
-// 182 x 512 x 2048 9.5 / 9.2; 207 x 1344 x 2048 9.6 / 10.7, 256 x 1344 x 3072 12.7 /
-// 13.8, 512 x 4096 x 2048 10.6 / 21.9; plain 342 x 64 x 4480 13.7 / 10.7, 446 x 71 x
-// 2720 11.0 / 9.7, 216 x 708 x 2560 8.7 / 10.0, 279 x 576 x 3584 10.6 / 11.6.
+// its K, about 3 ns a column with the residual and 2 without, and pays about 2.6 us a
+// million partial sums and 2 us.  With the residual 331 x 41 x 1152 7.7 / 8.2, 138 x
+// 160 x 1504 8.7 / 7.7, 868 x 224 x 1536 7.7 / 8.5, 167 x 384 x 1536 fp32 8.7 / 8.2, 944 x
+// 204 x 2112 fp32 11.2 / 9.8, 442 x 631 x 2048 11.5 / 12.5, 623 x 640 x 3072 12.6 / 13.7,
+// 340 x 2688 x 4000 21.5 / 17.5; plain 364 x 88 x 1536 5.9 / 6.6, 229 x 116 x 1920 7.7 /
+// 6.9, 190 x 453 x 2048 9.4 / 10.0, 210 x 344 x 2272 8.3 / 7.5, 317 x 544 x 2560 8.1 /
+// 8.6, 382 x 81 x 3584 11.6 / 9.8.
 static bool too_short_to_split(int64_t M, int64_t N, int64_t K, bool residual) {
   if (K > 4096) return false;
   if (K <= 1024) return true;
@@ -374,8 +375,8 @@ static bool too_short_to_split(int64_t M, int64_t N, int64_t K, bool residual) {
   const int64_t parts = splitk_plan(M, N, K).parts;
   if (parts < 2) return true;
   const int64_t saved = K - K / parts, sums = parts * M * N;
-  return residual ? saved <= std::max<int64_t>(1450, 775 + sums * 9 / 10000)
-                  : saved <= std::max<int64_t>(2200, 1240 + sums * 17 / 10000);
+  return residual ? saved <= std::max<int64_t>(800, 600 + sums * 9 / 10000)
+                  : saved <= std::max<int64_t>(1200, 1100 + sums * 13 / 10000);
 }
 
 int64_t gemm_split_bytes(int64_t M, int64_t N, int64_t K) {

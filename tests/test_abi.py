@@ -363,11 +363,14 @@ def test_gemm_split_at_short_k():
     assert w(213, 512, 3584) == 7 * 213 * 512 * 4
     assert w(278, 512, 2560) == 5 * 278 * 512 * 4
     assert w(150, 200, 2848) == 6 * 150 * 200 * 4          # ragged K
-    assert w(256, 1344, 3072) == 0                         # 2.1 M sums for 2560 columns
+    assert w(256, 1344, 3072) == 6 * 256 * 1344 * 4        # 2560 columns, 2.1 M sums
+    assert w(285, 1410, 3072) == 0                         # 2.4 M
     assert w(256, 4096, 4096) == 0                         # 64 tiles: 4.2 M sums
     assert w(182, 512, 2048) == 4 * 182 * 512 * 4          # 1536 columns, 0.4 M sums
     assert w(207, 1344, 2048) == 0                         # 1.1 M
-    assert w(521, 192, 1920) == 0                          # 1440 columns
+    assert w(521, 192, 1920) == 4 * 521 * 192 * 4          # 1440 columns
+    assert w(167, 384, 1536) == 3 * 167 * 384 * 4          # 1024
+    assert w(331, 41, 1152) == 0                           # 768
     assert w(502, 102, 1024) == 0 and w(1405, 320, 576) == 0
     assert w(99, 13632, 1216) == 0                         # 65-128 rows, wide N: from K = 2048
     assert w(100, 8192, 2048) == 4 * 100 * 8192 * 4

@@ -97,7 +97,8 @@ def test_tall_swiglu_tiles_from_their_shortest_k(K, residual):
 # Splits above 128 rows at short K: parts of 512 and of 1024 columns, the
 # residual split and the plain product not, and ragged K.
 @pytest.mark.parametrize("M,N,K", [(213, 512, 3584), (256, 576, 4096), (150, 200, 2848),
-                                   (1130, 200, 4096), (256, 1344, 3072)])
+                                   (1130, 200, 4096), (256, 1344, 3072), (285, 1410, 3072),
+                                   (167, 384, 1536), (331, 41, 1152), (521, 192, 1920)])
 @pytest.mark.parametrize("residual", [True, False])
 def test_split_at_short_k(orc, M, N, K, residual):
     q, w = _mx(M, N, K)
