@@ -906,9 +906,14 @@ int splitk_default_parts(int64_t M, int64_t N, int64_t K) {
 // of the 256 x 256 time where those tiles fill at most a quarter of the CUs
 // (129-256 rows x 12288 x 4096: 22-25 us against 40-43 us; 129-768 rows x
 // 4096 x 12288: 60-67 us against 108-117 us), 0.8-0.96 at 384-480 tiles,
-// 1.06-1.23 at 512-576.
-bool use_mid_tiles(int64_t M, int64_t N) {
-  return mid_tiles(M, N) < 2 * 256;
+// 1.06-1.23 at 512-576.  Also where they are many and K is at most two stages,
+// which is mostly prologue and epilogue, and those of a 256 x 256 tile nothing else
+// on its CU overlaps (256 x 256 / 128 x 128: 4205 rows x 4204 x 256 plain 18.1 / 14.5,
+// 2727 x 8724 x 256 plain 20.2 / 17.9, 2442 x 8447 x 192 plain 48.4 / 43.4; at 512 to
+// 1023 tiles 0.94 to 1.08).
+bool use_mid_tiles(int64_t M, int64_t N, int64_t K) {
+  const int64_t tiles = mid_tiles(M, N);
+  return tiles < 2 * 256 || (tiles >= 4 * 256 && K <= 2 * kStageK);
 }
 
 // Tall tiles where 128 x 128 ones number between one and two per CU and tall
@@ -949,7 +954,15 @@ bool use_tall_tiles(int64_t M, int64_t N, int64_t K, int64_t min_k) {
 // 44.3 -> 41.8, 300 x 4096 x 11008 37.3 -> 32.3; at 320 tiles (1000 rows x
 // 5000 x 2912), where three workgroups share a CU only without it, 29.7 ->
 // 33.1, at 384 and 480 no gain.  Four stages gave no more than two.
-bool use_deep_tiles(int64_t workgroups) { return workgroups <= 256; }
+// Not with the residual where a tile has up to four stages: what is read ahead then
+// is most of K, and the registers' writes cost more than the wait (one / two, W not
+// in L2: up to 128 tiles 0.97 to 1.00 of the time at K = 512, 0.93 to 0.97 below it at
+// any number; 497 rows x 704 x 512 with the SwiGLU epilogue 5.6 / 5.8 us; without the
+// residual and from K = 1024 1.00 to 1.08).
+bool use_deep_tiles(int64_t workgroups, int64_t K, bool residual) {
+  constexpr int64_t kFour = 4 * kStageK;
+  return workgroups <= 256 && !(residual && (K < kFour || (K == kFour && workgroups <= 128)));
+}
 
 }  // namespace
 
@@ -971,7 +984,7 @@ hipError_t launch_splitk_sum(const float *work, int parts, int64_t mn, void *z, 
 SplitPlan splitk_plan(int64_t M, int64_t N, int64_t K, int parts_wanted) {
   SplitPlan p{1, K, 0};
   const int64_t units = (K + kStageK * kGroup - 1) / (kStageK * kGroup);
-  if (!use_mid_tiles(M, N) || units < 2) return p;
+  if (!use_mid_tiles(M, N, K) || units < 2) return p;
   int want = parts_wanted;
   if (want <= 0) want = splitk_default_parts(M, N, K);
   if (want < 2) return p;
@@ -999,7 +1012,7 @@ hipError_t launch_gemm_large_split(const uint8_t *q_codes, const uint8_t *q_scal
     return launch_split<C, false>(q_codes, q_scales, r_codes, r_scales, w_codes, w_scales, M, N, K,
                                   z, z_bf16, work, plan.parts, plan.ksplit, stream);
   };
-  return use_deep_tiles(mid_tiles(M, N) * plan.parts) ? go(MidDeep{}) : go(Mid{});
+  return use_deep_tiles(mid_tiles(M, N) * plan.parts, plan.ksplit, r_codes != nullptr) ? go(MidDeep{}) : go(Mid{});
 }
 
 bool large_tiles_beat_few_rows(int64_t M, int64_t N) {
@@ -1035,17 +1048,19 @@ static int64_t big_tile_rows(int64_t M, int64_t N) {
 // Calls go(tile, first row, rows) for the tile shapes that M x N x K takes, with or
 // without a map.
 template <class Go>
-static hipError_t on_tiles(int64_t M, int64_t N, int64_t K, bool z_bf16, Go go) {
+static hipError_t on_tiles(int64_t M, int64_t N, int64_t K, bool residual, bool z_bf16, Go go) {
+  auto mid = [&](int64_t row0, int64_t rows) {
+    return use_deep_tiles(mid_tiles(rows, N), K, residual) ? go(MidDeep{}, row0, rows)
+                                                           : go(Mid{}, row0, rows);
+  };
   if (use_tall_tiles(M, N, K, tall_min_k(N, z_bf16))) return go(Tall{}, 0, M);
-  if (use_mid_tiles(M, N))
-    return use_deep_tiles(mid_tiles(M, N)) ? go(MidDeep{}, 0, M) : go(Mid{}, 0, M);
+  if (use_mid_tiles(M, N, K)) return mid(0, M);
   const int64_t big_rows = std::min<int64_t>(big_tile_rows(M, N) * Big::kBM, M);
   const hipError_t e = go(Big{}, 0, big_rows);
   if (e != hipSuccess || big_rows == M) return e;
   // Both tile shapes accumulate every output in the same order, so the
   // peeled rows carry the bits the 256 x 256 tiles would give them.
-  return use_deep_tiles(mid_tiles(M - big_rows, N)) ? go(MidDeep{}, big_rows, M - big_rows)
-                                                    : go(Mid{}, big_rows, M - big_rows);
+  return mid(big_rows, M - big_rows);
 }
 
 hipError_t launch_gemm_large(const uint8_t *q_codes, const uint8_t *q_scales,
@@ -1053,7 +1068,7 @@ hipError_t launch_gemm_large(const uint8_t *q_codes, const uint8_t *q_scales,
                              const uint8_t *w_codes, const uint8_t *w_scales,
                              int64_t M, int64_t N, int64_t K, void *z, bool z_bf16,
                              hipStream_t stream) {
-  return on_tiles(M, N, K, z_bf16, [&](auto tile, int64_t row0, int64_t rows) {
+  return on_tiles(M, N, K, r_codes != nullptr, z_bf16, [&](auto tile, int64_t row0, int64_t rows) {
     using C = decltype(tile);
     // Activation rows [row0, row0 + rows) and the same rows of Z.
     const uint8_t *qc = q_codes + row0 * (K / 2), *qs = q_scales + row0 * (K / 32);
@@ -1076,7 +1091,7 @@ hipError_t launch_gemm_large_phi(const uint8_t *q_codes, const uint8_t *q_scales
                                  const uint8_t *w_codes, const uint8_t *w_scales,
                                  const uint8_t *phi, int64_t M, int64_t N, int64_t K, void *z,
                                  bool z_bf16, hipStream_t stream) {
-  return on_tiles(M, N, K, z_bf16, [&](auto tile, int64_t row0, int64_t rows) {
+  return on_tiles(M, N, K, true, z_bf16, [&](auto tile, int64_t row0, int64_t rows) {
     using C = decltype(tile);
     // row0 is a multiple of 256: whole rows of the map.
     const int64_t co = row0 * (K / 2), so = row0 * (K / 32);
@@ -1115,9 +1130,9 @@ hipError_t launch_gemm_swiglu(const uint8_t *q_codes, const uint8_t *q_scales,
     return launch<C, false, true, true, false>(q_codes, q_scales, r_codes, r_scales, wgu_codes,
                                                wgu_scales, M, N, K, nullptr, stream, so);
   };
-  if (!use_mid_tiles(M, N)) return go(Big{});
+  if (!use_mid_tiles(M, N, K)) return go(Big{});
   if (use_tall_tiles(M, N, K, r_codes ? kTallSwigluMinK : kTallSwigluPlainMinK)) return go(Tall{});
-  return use_deep_tiles(mid_tiles(M, N)) ? go(MidDeep{}) : go(Mid{});
+  return use_deep_tiles(mid_tiles(M, N), K, r_codes != nullptr) ? go(MidDeep{}) : go(Mid{});
 }
 
 }  // namespace rfq

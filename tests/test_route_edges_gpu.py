@@ -94,6 +94,33 @@ def test_tall_swiglu_tiles_from_their_shortest_k(K, residual):
         assert torch.equal(a, b)
 
 
+# K of up to four stages: one stage in registers or two (with the residual from K =
+# 512 and 129 tiles two, below one), and from 1024 tiles 128 x 128 ones up to K = 256.
+@pytest.mark.parametrize("M,N,K", [(497, 704, 480), (497, 704, 512), (2048, 1024, 512),
+                                   (2049, 1024, 512), (4000, 4130, 256), (4205, 4204, 256),
+                                   (4205, 4204, 288), (8200, 2050, 32)])
+@pytest.mark.parametrize("residual", [True, False])
+def test_short_k_tiles(M, N, K, residual):
+    """The bits of the same rows in blocks of 256, whose tiles are few."""
+    q, w = _mx(M, N, K)
+    q = q if residual else (q[0], q[1], None, None)
+    print("short K: M=%d N=%d K=%d" % (M, N, K), flush=True)
+    phi = (torch.arange((M + 63) // 64, device="cuda") % 3 != 0).to(torch.uint8)
+    phi = phi[:, None].expand(-1, (K + 255) // 256).contiguous()
+    calls = [lambda q, phi, **kw: rfq.rfq_gemm(*q, *w, **kw)]
+    if residual:
+        calls.append(lambda q, phi, **kw: rfq.rfq_gemm_phi(*q, *w, phi, **kw))
+    for call in calls:
+        for dt in (torch.float32, torch.bfloat16):
+            z, intact = _guarded(M, N, dt)
+            call(q, phi, out=z)
+            for r in range(0, M, 256):
+                qr = [None if t is None else t[r:r + 256].clone() for t in q]
+                assert torch.equal(z[r:r + 256], call(qr, phi[r // 64:r // 64 + 4].clone(),
+                                                      out_dtype=dt))
+            assert intact()
+
+
 # Splits above 128 rows at short K: parts of 512 and of 1024 columns, the
 # residual split and the plain product not, and ragged K.
 @pytest.mark.parametrize("M,N,K", [(213, 512, 3584), (256, 576, 4096), (150, 200, 2848),
