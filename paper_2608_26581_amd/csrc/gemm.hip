@@ -324,8 +324,8 @@ hipError_t launch_tile(const uint8_t *qc, const uint8_t *qs, const uint8_t *rc,
 //
 // The few-row kernel takes the product (shape conditions only; alignment and
 // size conditions of the kernels are checked where they are dispatched).
-static bool few_rows_chosen(int64_t M, int64_t N) {
-  return M <= kSkinnyMaxRows && !large_tiles_beat_few_rows(M, N);
+static bool few_rows_chosen(int64_t M, int64_t N, int64_t K) {
+  return M <= kSkinnyMaxRows && !large_tiles_beat_few_rows(M, N, K);
 }
 
 // With a workspace the split product replaces the few-row kernel where it
@@ -381,7 +381,7 @@ static bool too_short_to_split(int64_t M, int64_t N, int64_t K, bool residual) {
 
 int64_t gemm_split_bytes(int64_t M, int64_t N, int64_t K) {
   if (M <= 0 || N <= 0 || K < 32 || (K % 32) != 0) return 0;
-  if (few_rows_chosen(M, N) && few_rows_beat_split(M, N, K)) {
+  if (few_rows_chosen(M, N, K) && few_rows_beat_split(M, N, K)) {
     const int parts = skinny_split_parts(M, N, K);
     return parts > 1 ? int64_t(parts) * M * N * 4 : 0;
   }
@@ -402,9 +402,9 @@ hipError_t launch_gemm(const uint8_t *q_codes, const uint8_t *q_scales,
     plan = splitk_plan(M, N, K);
     if (plan.work_bytes > work_bytes) plan = SplitPlan{1, K, 0};
   }
-  const bool split = plan.parts > 1 && !(few_rows_chosen(M, N) && few_rows_beat_split(M, N, K));
+  const bool split = plan.parts > 1 && !(few_rows_chosen(M, N, K) && few_rows_beat_split(M, N, K));
   if (gemm_skinny_applies(q_scales, r_scales, w_scales, M, N, K) && !split &&
-      !(large && large_tiles_beat_few_rows(M, N))) {
+      !(large && large_tiles_beat_few_rows(M, N, K))) {
     const int parts = work ? skinny_split_parts(M, N, K) : 1;
     if (parts > 1 && int64_t(parts) * M * N * 4 <= work_bytes)
       return launch_gemm_skinny_split(q_codes, q_scales, r_codes, r_scales, w_codes, w_scales, M,
@@ -443,7 +443,7 @@ hipError_t launch_gemm_phi(const uint8_t *q_codes, const uint8_t *q_scales,
   // 55.9 (50.5), 4096 x 5120 x 13824 (last tile rows 128-wide) 321 -> 296.
   const bool large = gemm_large_applies(q_scales, r_scales, w_scales, M, N, K);
   if (gemm_skinny_applies(q_scales, r_scales, w_scales, M, N, K) &&
-      !(large && large_tiles_beat_few_rows(M, N)))
+      !(large && large_tiles_beat_few_rows(M, N, K)))
     return launch_gemm_skinny_phi(q_codes, q_scales, r_codes, r_scales, w_codes, w_scales, phi, M,
                                   N, K, z, z_bf16, stream);
   if (large)

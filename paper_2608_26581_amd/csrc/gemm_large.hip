@@ -1015,7 +1015,8 @@ hipError_t launch_gemm_large_split(const uint8_t *q_codes, const uint8_t *q_scal
   return use_deep_tiles(mid_tiles(M, N) * plan.parts, plan.ksplit, r_codes != nullptr) ? go(MidDeep{}) : go(Mid{});
 }
 
-bool large_tiles_beat_few_rows(int64_t M, int64_t N) {
+bool large_tiles_beat_few_rows(int64_t M, int64_t N, int64_t K) {
+  if (M > 32 && N >= 16384 && K <= 2048 && K % 512) return true;
   return M > 64 && (N + Mid::kBN - 1) / Mid::kBN >= 96;
 }
 

@@ -111,8 +111,11 @@ hipError_t launch_gemm_static_scratch(const uint8_t *q_codes, const uint8_t *q_s
 // are faster than the few-row kernel once there are at least 96 column tiles
 // (N > 12160): measured 0.45-0.77 of its time at 80-128 rows and N = 12288,
 // 13824 and 24576; 1.3-3x slower at N = 4096-5120, where one row of tiles
-// occupies 32-40 CUs.
-bool large_tiles_beat_few_rows(int64_t M, int64_t N);
+// occupies 32-40 CUs.  At ragged K up to 2048 and from N = 16384 also from 33 rows:
+// few-row / 128-wide us 41 x 31716 x 128 9.0 / 4.9, 55 x 21815 x 416 plain 9.0 / 5.9,
+// 46 x 23040 x 192 8.6 / 5.3 (0.57 of its time up to K = 256, 0.78 at 1024 to 2048;
+// 11264 <= N < 16384 0.82 up to 256, 1.04 to 1.4 beyond; up to 32 rows 0.85 to 1.6).
+bool large_tiles_beat_few_rows(int64_t M, int64_t N, int64_t K);
 
 // Product for few activation rows (M <= kSkinnyMaxRows, 16-byte aligned scale tensors, code tensors below 2 GiB): one workgroup per
 // 16, 32 or 64 weight rows and up to 64 activation rows.

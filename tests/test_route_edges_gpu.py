@@ -121,6 +121,29 @@ def test_short_k_tiles(M, N, K, residual):
             assert intact()
 
 
+# Ragged K, 33 to 64 rows: the few-row kernel below N = 16384, 128-wide tiles from
+# there (to K = 2048).
+@pytest.mark.parametrize("M,N,K", [(32, 16390, 96), (33, 16380, 96), (33, 16384, 96),
+                                   (64, 16390, 416), (50, 16388, 2016), (50, 16388, 2080)])
+@pytest.mark.parametrize("residual", [True, False])
+def test_few_rows_wide_at_ragged_k(orc, M, N, K, residual):
+    q, w = _mx(M, N, K)
+    q = q if residual else (q[0], q[1], None, None)
+    print("few rows, ragged K: M=%d N=%d K=%d" % (M, N, K), flush=True)
+    z, intact = _guarded(M, N, torch.float32)
+    rfq.rfq_gemm(*q, *w, out=z)
+    rows = np.unique(np.r_[0:3, 30:33, M - 2:M].clip(0, M - 1))
+    zr, bound = orc.gemm(*[None if t is None else host(t)[rows] for t in q], host(w[0]),
+                         host(w[1]))
+    assert_gemm_close(host(z)[rows], zr, bound, False, "product")
+    assert intact()
+    zb = rfq.rfq_gemm(*q, *w, out_dtype=torch.bfloat16, split=True)
+    assert torch.equal(zb, z.bfloat16())
+    if residual:
+        ones = torch.ones((1, (K + 255) // 256), dtype=torch.uint8, device="cuda")
+        assert torch.equal(rfq.rfq_gemm_phi(*q, *w, ones), z)
+
+
 # Splits above 128 rows at short K: parts of 512 and of 1024 columns, the
 # residual split and the plain product not, and ragged K.
 @pytest.mark.parametrize("M,N,K", [(213, 512, 3584), (256, 576, 4096), (150, 200, 2848),
