@@ -94,10 +94,11 @@ def test_tall_swiglu_tiles_from_their_shortest_k(K, residual):
         assert torch.equal(a, b)
 
 
-# K of up to four stages: one stage in registers or two (with the residual from K =
-# 512 and 129 tiles two, below one), and from 1024 tiles 128 x 128 ones up to K = 256.
+# K of up to eight stages: one stage in registers or two (with the residual two
+# from K = 512 and 129 tiles, K = 544 and 65, K = 1056), and from 1024 tiles 128 x 128 ones up to K = 256.
 @pytest.mark.parametrize("M,N,K", [(497, 704, 480), (497, 704, 512), (2048, 1024, 512),
-                                   (2049, 1024, 512), (4000, 4130, 256), (4205, 4204, 256),
+                                   (2049, 1024, 512), (1024, 1024, 544), (1025, 1024, 544),
+                                   (300, 500, 1024), (300, 500, 1056), (4000, 4130, 256), (4205, 4204, 256),
                                    (4205, 4204, 288), (8200, 2050, 32)])
 @pytest.mark.parametrize("residual", [True, False])
 def test_short_k_tiles(M, N, K, residual):
