@@ -137,9 +137,9 @@ rfq_status rfq_gemm(const uint8_t *q_codes, const uint8_t *q_scales,
  * up to 1024; up to 128 rows, from N = 512, up to 3072 (N <= 4096; up to 4096
  * with up to 64 rows) or below 2048 (wider N; up to 2048 with up to 64 rows);
  * with more rows and K <= 4096 where the partial sums cost more than the
- * columns saved, K - K / parts (at least 800 columns, and 600 and 900 a million
- * partial sums; for a plain product 1200, and 1100 and 1300 a million: it may
- * run unsplit where the RFQ product splits).  Where the few-row grid's last
+ * columns saved, K - K / parts (these must pass 800 and 600 + 900 s with s
+ * million partial sums; for a plain product 1200 and 1100 + 1300 s: it may run
+ * unsplit where the RFQ product splits).  Where the few-row grid's last
  * round of workgroups is at most a quarter full (e.g. N = 5120) with up to
  * 16 rows and K >= 12288, the few-row product itself splits K in three
  * parts.
