@@ -934,11 +934,14 @@ constexpr int64_t kTallMinK = 1024, kTallSwigluMinK = 2048, kTallSwigluPlainMinK
 // pieces, the longest epilogue of the product: from K = 2048 (bf16 272 rows x 11019 x
 // 1024 16.3 / 20.7, 4515 x 1365 x 1536 24.6 / 26.2, 302 x 10927 x 1536 plain 15.1 /
 // 19.3, fp32 20.2 / 23.0; bf16 566 x 6860 x 2048 plain 16.7 / 13.9, 664 x 7924 x 2048
-// 21.6 / 20.4, 888 x 6611 x 2048 29.7 / 30.2).  Not with one tile row, where the other shape has
-// two (153 x 28884 x 2784 35.6 / 26.2; 129 to 256 rows at K = 1024 to 2047 1.06 to 1.2
-// of its time).
-constexpr int64_t kTallBrokenRowsMinK = 2048;
+// 21.6 / 20.4, 888 x 6611 x 2048 29.7 / 30.2).  Not with one tile row, where the other
+// shape has two: up to 192 rows from K = 512, whole rows of Z too (153 x 28884 x 2784
+// 35.6 / 26.2, 165 x 18753 x 512 plain 15.4 / 11.0, 147 x 18176 x 512 7.5 / 7.0; 129 to 192
+// rows at K = 512 to 1023 1.05 to 1.23 of its time, 193 to 256 0.95 to 1.02, below K =
+// 512 0.92 to 1.27).
+constexpr int64_t kTallBrokenRowsMinK = 2048, kTallOneRowMinK = 512, kTallOneRowMaxM = 192;
 int64_t tall_min_k(int64_t M, int64_t N, bool z_bf16) {
+  if (M <= kTallOneRowMaxM) return kTallOneRowMinK;
   return N % (z_bf16 ? 8 : 4) && M > Tall::kBM ? kTallBrokenRowsMinK : kTallMinK;
 }
 bool use_tall_tiles(int64_t M, int64_t N, int64_t K, int64_t min_k) {
@@ -957,15 +960,16 @@ bool use_tall_tiles(int64_t M, int64_t N, int64_t K, int64_t min_k) {
 // 5000 x 2912), where three workgroups share a CU only without it, 29.7 ->
 // 33.1, at 384 and 480 no gain.  Four stages gave no more than two.
 // Not where a tile has so few stages that what is read ahead is most of K, and the
-// registers' writes cost more than the wait (one / two, W not in L2): with the
-// residual 0.93 to 0.97 of the time below K = 512 at any number, 0.97 to 1.00 up to 128
-// tiles at 512, 0.98 to 0.99 up to 64 (W in L2, where 3 rows x 64 x 1024 with the SwiGLU
-// epilogue took 6.5 / 6.75 us) at 1024; without it 0.98 to 1.00 up to 64 tiles to K = 512
-// (211 x 64 x 512 with that epilogue 4.0 / 4.2).  Beyond, 1.00 to 1.08.
+// registers' writes cost more than the wait (one / two; of the time, W not in L2, or
+// us, W in L2): with the residual 0.93 to 0.97 below K = 512 at any number, 0.97 to 1.02
+// at 512 (3 rows x 19904 x 512 with the SwiGLU epilogue 5.35 / 5.55 us), 0.98 to 0.99 up
+// to 64 tiles at 1024 (3 x 64 x 1024 with that epilogue 6.5 / 6.75 us); without it 0.98
+// to 1.00 up to 64 tiles to K = 512 (211 x 64 x 512 with it 4.0 / 4.2 us).  Beyond, 1.00
+// to 1.08.
 bool use_deep_tiles(int64_t workgroups, int64_t K, bool residual) {
   if (workgroups > 256) return false;
   if (!residual) return K > 512 || workgroups > 64;
-  return K > 1024 || (K > 512 && workgroups > 64) || (K == 512 && workgroups > 128);
+  return K > 1024 || (K > 512 && workgroups > 64);
 }
 
 }  // namespace
