@@ -419,8 +419,9 @@ rfq_status rfq_hif4_gemm_wbf16(const uint8_t *q_codes, const uint32_t *q_meta,
  * weights decoded to bf16 (N * K * 2 bytes, at most 1 GiB, in an order of the
  * library's own) and is multiplied from there: the bits of rfq_hif4_gemm,
  * without decoding W again for every 128 rows.  Where that is not faster (up to
- * 256 tiles of 128 x 128; a plain product with K < 576, 384 below N = 2048, and
- * fewer than 256 tiles of 128 x 256) the workspace stays unused.
+ * 256 tiles of 128 x 128, except with the residual where N is not a multiple of 32,
+ * K >= 8192 and M >= 2048; a plain product with K < 576, 384 below N = 2048, and fewer than
+ * 256 tiles of 128 x 256) the workspace stays unused.
  * Each part of K writes its fp32 partial
  * sums to the workspace; one pass then adds the parts in a fixed order and
  * rounds to z_dtype, so the result is deterministic but its fp32 summation

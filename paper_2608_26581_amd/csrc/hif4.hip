@@ -1634,10 +1634,13 @@ SplitPlan hif4_split_plan(int64_t M, int64_t N, int64_t K) {
 // 17.6, 1253 x 3424 x 768 22.8 / 23.3), below N = 2048, where W's decode is short,
 // from 384 (7316 x 608 x 192 12.1 / 10.1, 3607 x 1184 x 384 14.05 / 14.4, x 512 15.7 /
 // 16.8), with the residual at every K (4410 x 992 x 128 12.2 / 12.9, 1347 x 3328 x
-// 448 22.2 / 24.1), as both with more tiles (4368 x 1920 x 512 plain 27.1 / 32.4).
+// 448 22.2 / 24.1), as both with more tiles (4368 x 1920 x 512 plain 27.1 / 32.4).  Row
+// by row (N not a multiple of 32) it also pays with the residual at one tile per CU
+// from K = 8192 and 2048 rows (4749 x 507 x 13824 217 / 231, 1100 x 2500 x 8192 145 /
+// 141; at K = 4096 to 8191 0.98 to 1.01 of the time, below 1.03 to 1.15).
 static bool decoded_w_pays(int64_t M, int64_t N, int64_t K, bool residual) {
-  const int64_t rows = (M + kBM - 1) / kBM;
-  if (rows * ((N + 127) / 128) <= kFillTiles) return false;
+  const int64_t rows = (M + kBM - 1) / kBM, tiles = rows * ((N + 127) / 128);
+  if (tiles <= kFillTiles) return residual && N % 32 && K >= 8192 && M >= 2048;
   return residual || K >= (N < 2048 ? 384 : 576) || rows * ((N + 255) / 256) >= kFillTiles;
 }
 

@@ -61,14 +61,16 @@ def test_fp32_rows(M, N, K, residual):
 
 
 # 256 x 128 tiles from K = 1024 (SwiGLU epilogue: 2048, plain 1536; rows of Z
-# that do not start at 16 bytes: 2048), 128 x 128 below.
+# that do not start at 16 bytes: 2048; up to 192 rows: 512), 128 x 128 below.
 @pytest.mark.parametrize("M,N,K", [(300, 12300, 992), (300, 12300, 1024), (520, 7200, 512),
-                                   (300, 12301, 1024), (300, 12301, 2016), (300, 12301, 2048)])
+                                   (300, 12301, 1024), (300, 12301, 2016), (300, 12301, 2048),
+                                   (192, 16500, 480), (192, 16500, 512), (193, 16500, 512),
+                                   (256, 16501, 1024)])
 def test_tall_tiles_from_their_shortest_k(orc, M, N, K):
     q, w = _mx(M, N, K)
     print("tall tiles: M=%d N=%d K=%d" % (M, N, K), flush=True)
     z = host(rfq.rfq_gemm(*q, *w))
-    rows = np.unique(np.r_[0:4, 255:258, M - 3:M, 130:M:29])
+    rows = np.unique(np.r_[0:4, 255:258, M - 3:M, 130:M:29].clip(0, M - 1))
     zr, bound = orc.gemm(*[host(t)[rows] for t in q], host(w[0]), host(w[1]))
     assert_gemm_close(z[rows], zr, bound, False, "product")
     ones = torch.ones(((M + 63) // 64, (K + 255) // 256), dtype=torch.uint8, device="cuda")
@@ -95,7 +97,7 @@ def test_tall_swiglu_tiles_from_their_shortest_k(K, residual):
 
 
 # K of up to eight stages: one stage in registers or two (with the residual two
-# from K = 512 and 129 tiles, K = 544 and 65, K = 1056), and from 1024 tiles 128 x 128 ones up to K = 256.
+# from K = 544 and 65 tiles, K = 1056), and from 1024 tiles 128 x 128 ones up to K = 256.
 @pytest.mark.parametrize("M,N,K", [(497, 704, 480), (497, 704, 512), (2048, 1024, 512),
                                    (2049, 1024, 512), (1024, 1024, 544), (1025, 1024, 544),
                                    (300, 500, 1024), (300, 500, 1056), (4000, 4130, 256), (4205, 4204, 256),
@@ -194,10 +196,13 @@ def test_hif4_plain_tiles_two_per_cu(M, N, K):
 
 # Both sides of where W is decoded into the workspace: 256 tiles of 128 x 128 (not)
 # and 257 or more; the plain product with K = 512 (not) and 576, below N =
-# 2048 320 (not) and 384, up to 256 tiles of 128 x 256; N not a multiple of 32 (row by row).
+# 2048 320 (not) and 384, up to 256 tiles of 128 x 256; N not a multiple of 32 (row by row, with the
+# residual from K = 8192 and 2048 rows at fewer tiles too).
 @pytest.mark.parametrize("M,N,K", [(1024, 4096, 192), (1025, 4064, 192), (1300, 4224, 512),
                                    (1300, 4224, 576), (1025, 4100, 512), (1025, 4100, 576),
-                                   (4100, 4096, 192), (3600, 1184, 320), (3600, 1184, 384)])
+                                   (4100, 4096, 192), (3600, 1184, 320), (3600, 1184, 384),
+                                   (2100, 1250, 8128), (2047, 1250, 8192), (2100, 1250, 8192),
+                                   (2100, 1248, 8192)])
 @pytest.mark.parametrize("residual", [True, False])
 def test_hif4_decoded_weights_from_their_smallest_sizes(M, N, K, residual):
     q, w = _hif4(M, N, K)
@@ -213,6 +218,7 @@ def test_hif4_decoded_weights_from_their_smallest_sizes(M, N, K, residual):
     # The line lies where the comments say: the workspace is written or not.
     tiles, wide = -(-M // 128) * -(-N // 128), -(-M // 128) * -(-N // 256)
     used = tiles > 256 and (residual or K >= (384 if N < 2048 else 576) or wide >= 256)
+    used |= tiles <= 256 and residual and N % 32 != 0 and K >= 8192 and M >= 2048
     assert bool((ws[:nbytes] != 0x5A).any()) == used
 
 
